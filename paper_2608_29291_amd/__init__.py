@@ -133,6 +133,8 @@ _sig("ce_ffn_saliency", ctypes.c_int, [ctypes.POINTER(CEBatch), _p, _p, _p, ctyp
                                        ctypes.c_float, _p, _p, _p, _p, ctypes.c_size_t, _p])
 _sig("ce_ffn_mask_channels", ctypes.c_int, [ctypes.POINTER(CEBatch), _p, _p, ctypes.c_int, _i32, _p, _p, _p])
 _sig("ce_routed_attention", ctypes.c_int, [ctypes.POINTER(CEAttn), _p, _p, _p, _p, _p])
+_sig("ce_attention_workspace_size", ctypes.c_size_t, [ctypes.POINTER(CEAttn)])
+_sig("ce_routed_attention_ws", ctypes.c_int, [ctypes.POINTER(CEAttn), _p, _p, _p, _p, _p, ctypes.c_size_t, _p])
 _sig("ce_score_tiling", ctypes.c_int, [ctypes.POINTER(CEBatch), ctypes.POINTER(CEScorerW), _p])
 _sig("ce_layer_gap", ctypes.c_int, [ctypes.POINTER(CEBatch), _p, _p, ctypes.c_int, _i32, _p, ctypes.c_float,
                                     _p, _p, _p, _p, _p, _p])
@@ -683,8 +685,14 @@ def ce_routed_attention(q, k, v, o, q_offsets, kv_offsets, causal, scale, stream
             _chk(kv_offsets, "kv_offsets", torch.int32, numel=2))
     at = CEAttn(B, qs[1], ks[1], qs[2], ptrs[4], ptrs[5], qs[0], ks[0], int(bool(causal)), float(scale),
                 _dtype_code(q))
-    _check(lib.ce_routed_attention(ctypes.byref(at), ptrs[0], ptrs[1], ptrs[2], ptrs[3], _stream(stream)),
-           "ce_routed_attention")
+    # partial results of a decode step's key chunks: stream-ordered scratch
+    # from torch's allocator, on the stream that the kernels run on
+    ws, need = None, int(lib.ce_attention_workspace_size(ctypes.byref(at)))
+    if need:
+        with torch.cuda.stream(stream):  # None: the current stream
+            ws = torch.empty(need, dtype=torch.uint8, device=q.device)
+    _check(lib.ce_routed_attention_ws(ctypes.byref(at), ptrs[0], ptrs[1], ptrs[2], ptrs[3], _ptr(ws), need,
+                                      _stream(stream)), "ce_routed_attention")
 
 
 __all__ = [

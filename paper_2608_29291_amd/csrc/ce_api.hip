@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "ce_host.hpp"
+#include "ce_router_attn_ws.h"
 #include <math.h>
 
 #include "ce_launch.hpp"
@@ -311,6 +312,42 @@ int routed_block_impl(const ce_batch* batch, const void* hidden_in, void* hidden
   return finish_gap();
 }
 
+// Routed attention; ws may be NULL (long caches are then not cut into chunks).
+int attention_impl(const ce_attn* at, const void* q, const void* k, const void* v, void* o, void* ws, size_t ws_bytes,
+                   void* stream) {
+  if (!at) return CE_ERR_INVALID_ARG;
+  if (at->B < 1 || at->n_heads < 1 || at->n_kv_heads < 1 || at->q_capacity < 0 || at->kv_capacity < 0)
+    return CE_ERR_INVALID_ARG;
+  if (at->n_heads % at->n_kv_heads != 0) return CE_ERR_INVALID_ARG;
+  if (at->causal != 0 && at->causal != 1) return CE_ERR_INVALID_ARG;
+  if (!isfinite(at->scale) || !(at->scale > 0.0f)) return CE_ERR_INVALID_ARG;
+  if (!at->q_offsets || !at->kv_offsets) return CE_ERR_INVALID_ARG;
+  if (at->dtype != CE_BF16 || at->head_dim != 128) return CE_ERR_UNSUPPORTED;
+  const int64_t lim = (int64_t)1 << 31;
+  if ((int64_t)at->q_capacity * at->n_heads * 256 >= lim || (int64_t)at->kv_capacity * at->n_kv_heads * 256 >= lim)
+    return CE_ERR_UNSUPPORTED;
+  if (at->q_capacity > 0 && (!q || !o)) return CE_ERR_INVALID_ARG;
+  if (at->q_capacity > 0 && at->kv_capacity > 0 && (!k || !v)) return CE_ERR_INVALID_ARG;
+  const AttnSplit sp = attention_split(at->B, at->n_heads, at->n_kv_heads, at->q_capacity, at->kv_capacity, true);
+  if (ws && sp.bytes > 0) CE_CHECK(check_ws(ws, ws_bytes, sp.bytes));
+  const auto* cq = static_cast<const char*>(q);
+  const auto* ck = static_cast<const char*>(k);
+  const auto* cv = static_cast<const char*>(v);
+  auto* co = static_cast<char*>(o);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  // Few queries (decode): the key/value heads' groups as rows, the keys cut;
+  // else 128 queries of one head per workgroup (prefill, generation). The line
+  // lies where the sequences' rows fill one 32-column operand on average: a
+  // decode step is 90 us on the 128-query kernel and 21 us on the other, and
+  // above it the other would read the keys once more per 32 rows.
+  if (sp.few)
+    return hip_status(launch_attention_decode(cq, ck, cv, co, at->q_offsets, at->kv_offsets, at->B, at->n_heads,
+                                              at->n_kv_heads, at->q_capacity, at->kv_capacity, at->causal != 0,
+                                              at->scale, sp.bytes > 0 ? ws : nullptr, s));
+  return hip_status(launch_attention(cq, ck, cv, co, at->q_offsets, at->kv_offsets, at->B, at->n_heads,
+                                     at->n_kv_heads, at->q_capacity, at->kv_capacity, at->causal != 0, at->scale, s));
+}
+
 }  // namespace
 
 extern "C" {
@@ -598,23 +635,12 @@ int ce_layer_gap(const ce_batch* batch, const void* x_in, const void* x_out, int
 }
 
 int ce_routed_attention(const ce_attn* at, const void* q, const void* k, const void* v, void* o, void* stream) {
-  if (!at) return CE_ERR_INVALID_ARG;
-  if (at->B < 1 || at->n_heads < 1 || at->n_kv_heads < 1 || at->q_capacity < 0 || at->kv_capacity < 0)
-    return CE_ERR_INVALID_ARG;
-  if (at->n_heads % at->n_kv_heads != 0) return CE_ERR_INVALID_ARG;
-  if (at->causal != 0 && at->causal != 1) return CE_ERR_INVALID_ARG;
-  if (!isfinite(at->scale) || !(at->scale > 0.0f)) return CE_ERR_INVALID_ARG;
-  if (!at->q_offsets || !at->kv_offsets) return CE_ERR_INVALID_ARG;
-  if (at->dtype != CE_BF16 || at->head_dim != 128) return CE_ERR_UNSUPPORTED;
-  const int64_t lim = (int64_t)1 << 31;
-  if ((int64_t)at->q_capacity * at->n_heads * 256 >= lim || (int64_t)at->kv_capacity * at->n_kv_heads * 256 >= lim)
-    return CE_ERR_UNSUPPORTED;
-  if (at->q_capacity > 0 && (!q || !o)) return CE_ERR_INVALID_ARG;
-  if (at->q_capacity > 0 && at->kv_capacity > 0 && (!k || !v)) return CE_ERR_INVALID_ARG;
-  return hip_status(launch_attention(static_cast<const char*>(q), static_cast<const char*>(k),
-                                     static_cast<const char*>(v), static_cast<char*>(o), at->q_offsets,
-                                     at->kv_offsets, at->B, at->n_heads, at->n_kv_heads, at->q_capacity,
-                                     at->kv_capacity, at->causal != 0, at->scale, static_cast<hipStream_t>(stream)));
+  return attention_impl(at, q, k, v, o, nullptr, 0, stream);
+}
+
+int ce_routed_attention_ws(const ce_attn* at, const void* q, const void* k, const void* v, void* o, void* ws,
+                           size_t ws_bytes, void* stream) {
+  return attention_impl(at, q, k, v, o, ws, ws_bytes, stream);
 }
 
 }  // extern "C"

@@ -1,6 +1,7 @@
 // Host-only part of the C ABI (validation, workspace layout, keep-count rule,
 // status strings). Pure C++: no HIP headers.
 #include "ce_host.hpp"
+#include "ce_router_attn_ws.h"
 
 #include <math.h>
 #include <string.h>
@@ -44,6 +45,27 @@ GemmSplit gemm_split(int64_t items, int ns) {
   sp.whole_x = full;
   sp.tail_x = tail;
   sp.pieces = best_s;
+  return sp;
+}
+
+AttnSplit attention_split(int B, int H, int Hkv, int q_cap, int kv_cap, bool with_ws) {
+  AttnSplit sp;
+  memset(&sp, 0, sizeof(sp));
+  const int64_t g = H / Hkv;
+  sp.few = (int64_t)q_cap * g <= (int64_t)kAttnRows * B;
+  const int64_t target = 2 * kXcdCount * kCusPerXcd;
+  int64_t chunk = ((int64_t)kv_cap * Hkv + target - 1) / target;
+  chunk = (chunk + 127) / 128 * 128;
+  if (chunk < 128) chunk = 128;
+  if (!with_ws) chunk = (int64_t)1 << 30;
+  sp.chunk = (int)chunk;
+  // a sequence's keys or rows end in at most one partial item
+  sp.items = (int)(kv_cap / chunk + (int64_t)q_cap * g / kAttnRows + B);
+  sp.cuts = kv_cap > chunk;
+  if (sp.few && sp.cuts) {
+    sp.part_off = align_up((size_t)B * 4);
+    sp.bytes = sp.part_off + (size_t)sp.items * Hkv * kAttnRows * (128 + 2) * 4;
+  }
   return sp;
 }
 
@@ -292,6 +314,17 @@ size_t ce_workspace_size(int which, const ce_batch* batch, int32_t d, int32_t d_
   const int elem = ce::elem_size(dtype);
   if (!elem) return 0;
   return ce::ws_layout(which, batch->B, batch->T, batch->kept_capacity, d, d_ff, elem).total;
+}
+
+size_t ce_attention_workspace_size(const ce_attn* at) {
+  if (!at || at->B < 1 || at->n_heads < 1 || at->n_kv_heads < 1 || at->n_heads % at->n_kv_heads != 0 ||
+      at->q_capacity < 0 || at->kv_capacity < 0)
+    return 0;
+  // over the entry points' size limits: nothing to run
+  const int64_t lim = (int64_t)1 << 31;
+  if ((int64_t)at->q_capacity * at->n_heads * 256 >= lim || (int64_t)at->kv_capacity * at->n_kv_heads * 256 >= lim)
+    return 0;
+  return ce::attention_split(at->B, at->n_heads, at->n_kv_heads, at->q_capacity, at->kv_capacity, true).bytes;
 }
 
 }  // extern "C"

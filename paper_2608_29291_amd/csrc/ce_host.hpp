@@ -101,6 +101,24 @@ int score_token_tile(int B, int T, int d, int r_core, int r_exp, int elem);
 constexpr int kScoreMaxTiles = 10;  // ceil(r_core / 64) + ceil(r_exp / 64) with r_core + r_exp <= 512
 int score_tiling(int B, int T, int d, int r_core, int r_exp, int elem, int* tm, int* tn, int* n_ct, int* n_rt);
 
+// Routed attention for few queries per sequence (ce_attention_decode.hip):
+// the query heads that share a key/value head are rows of one operand, and
+// `few` says that the sequences' rows fit a work item of kAttnRows on average.
+// Keys are cut into chunks so that about two workgroups run on each of the 256
+// CUs (few enough that all are resident, so the whole cache is in flight), of
+// at least 128 keys, one tile of 32 for each wave of a workgroup. Without a
+// workspace no sequence is cut.
+constexpr int kAttnRows = 32;
+struct AttnSplit {
+  int few;          // 1: this kernel's shape of call
+  int chunk;        // keys per work item
+  int items;        // work items per key/value head, at most
+  int cuts;         // 1 when a sequence can have more keys than a chunk
+  size_t part_off;  // workspace: int32 [B] first items, then the partial results
+  size_t bytes;     // workspace bytes (0: none needed)
+};
+AttnSplit attention_split(int B, int H, int Hkv, int q_cap, int kv_cap, bool with_ws);
+
 int elem_size(int dtype);  // 2 for bf16, 4 for f32, 0 if unknown
 
 int32_t num_keep_host(float keep, int32_t n);

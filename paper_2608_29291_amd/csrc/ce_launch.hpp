@@ -220,4 +220,10 @@ hipError_t launch_attention(const char* q, const char* k, const char* v, char* o
                             const int32_t* kv_offsets, int B, int H, int Hkv, int q_cap, int kv_cap, bool causal,
                             float scale, hipStream_t stream);
 
+// The same for few queries per sequence (attention_split); ws: its workspace,
+// or NULL (no sequence is cut).
+hipError_t launch_attention_decode(const char* q, const char* k, const char* v, char* o, const int32_t* q_offsets,
+                                   const int32_t* kv_offsets, int B, int H, int Hkv, int q_cap, int kv_cap, bool causal,
+                                   float scale, void* ws, hipStream_t stream);
+
 }  // namespace ce

@@ -1,0 +1,92 @@
+"""Routed attention with few queries per sequence (decode and speculative
+steps over the compressed cache) against the float64 oracle, at the sizes where
+the key chunks, the 32-key tiles and the 32 (query, head) rows of a work item
+end. Tolerance as in test_gpu_attention.py: the probabilities' and the output's
+bf16 roundings, 2^-8 max|v|; adding the chunks' fp32 results changes neither.
+"""
+import numpy as np
+import pytest
+
+from ce_workloads import make_attention_inputs
+from oracle import attention as oa
+
+pytestmark = pytest.mark.gpu
+DH = 128
+
+
+def run(q, k, v, qo, ko, causal, ws=True):
+    import ctypes
+    import torch
+    import gpu_util as G
+    import paper_2608_29291_amd as ce
+    bf = torch.bfloat16
+    dq, dk, dv, dqo, dko = G.to_dev(q, bf), G.to_dev(k, bf), G.to_dev(v, bf), G.to_dev(qo), G.to_dev(ko)
+    o = torch.full(dq.shape, float("nan"), dtype=bf, device="cuda")
+    if ws:
+        ce.ce_routed_attention(dq, dk, dv, o, dqo, dko, causal, DH ** -0.5)
+    else:  # the C entry point without a workspace: no sequence is cut
+        at = ce.CEAttn(len(qo) - 1, q.shape[1], k.shape[1], DH, dqo.data_ptr(), dko.data_ptr(), len(q), len(k),
+                       int(causal), DH ** -0.5, ce.CE_BF16)
+        st = ce.lib.ce_routed_attention(ctypes.byref(at), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), o.data_ptr(),
+                                        torch.cuda.current_stream().cuda_stream)
+        assert st == ce.CE_OK
+    torch.cuda.synchronize()
+    return G.host(o)
+
+
+CASES = {
+    # one query: cache ends at the edges of tiles and chunks
+    "edges": ([1] * 9, [1, 31, 32, 33, 127, 128, 129, 256, 1000], 12, 2),
+    "long": ([1, 1], [5003, 40], 28, 4),
+    "ungrouped": ([1, 1, 1], [700, 300, 129], 4, 4),
+    "wide_group": ([1, 1], [900, 257], 32, 1),  # all 32 rows of an item
+    # several queries: 4 x 7 rows fit an item, 5 x 7 need two (that sequence is not cut)
+    "speculative": ([4, 1, 5, 2, 0, 1, 3, 1], [900, 1300, 700, 2, 400, 0, 333, 650], 28, 4),
+    # all queries in one sequence of many; more queries than keys
+    "skewed": ([40] + [0] * 7 + [1] * 40, [600] + [9] * 7 + [35] * 40, 12, 2),
+    "short_cache": ([3, 2], [1, 2], 12, 2),
+    "many": ([1] * 600, [(7 * i) % 90 for i in range(600)], 4, 2),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+@pytest.mark.parametrize("causal", [False, True])
+def test_few_queries(name, causal):
+    ql, kl, h, hkv = CASES[name]
+    assert sum(ql) * (h // hkv) <= 32 * len(ql)  # the shape of call that takes this kernel
+    q, k, v, qo, ko = make_attention_inputs(ql, kl, h, hkv, DH, seed=len(name))
+    ref = oa.attention(q, k, v, qo, ko, hkv, causal, DH ** -0.5)
+    tol = 2.0 ** -8 * float(np.max(np.abs(v))) + 1e-6
+    for ws in (True, False):
+        got = run(q, k, v, qo, ko, causal, ws)
+        err = float(np.max(np.abs(got - ref)))
+        print(f"[decode {name} causal={causal} ws={ws}] max err {err:.3e} (bar {tol:.3e})", flush=True)
+        assert err <= tol
+        np.testing.assert_array_equal(got, run(q, k, v, qo, ko, causal, ws))
+
+
+def test_own_stream_and_capture():
+    """On another stream, and captured with replays between eager calls."""
+    import torch
+    import gpu_util as G
+    import paper_2608_29291_amd as ce
+    ql, kl, h, hkv = CASES["long"]
+    q, k, v, qo, ko = make_attention_inputs(ql, kl, h, hkv, DH, seed=3)
+    want = run(q, k, v, qo, ko, True)
+    bf = torch.bfloat16
+    args = [G.to_dev(q, bf), G.to_dev(k, bf), G.to_dev(v, bf)]
+    o, dqo, dko = torch.zeros_like(args[0]), G.to_dev(qo), G.to_dev(ko)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    ce.ce_routed_attention(*args, o, dqo, dko, True, DH ** -0.5, stream=side)
+    side.synchronize()
+    np.testing.assert_array_equal(G.host(o), want)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ce.ce_routed_attention(*args, o, dqo, dko, True, DH ** -0.5)
+    for _ in range(3):
+        o.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(G.host(o), want)
+        run(q, k, v, qo, ko, False)
