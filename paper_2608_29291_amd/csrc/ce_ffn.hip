@@ -1286,8 +1286,15 @@ inline int64_t grid_tiles(const FfnGemmArgs& a, int feat_tile, int tok_tile) {
   return (int64_t)((a.cap + tok_tile - 1) / tok_tile + a.n_sets - 1) * ((a.n_feat + feat_tile - 1) / feat_tile);
 }
 
+// At most kFewRows rows without the pruning signal: the kernel that streams
+// each weight once past registers holding all rows.
+inline bool few_ok(const FfnGemmArgs& a) {
+  return a.cap <= kFewRows && !a.sal_part && !a.row_flag && pp2_ok(a) && a.n_feat % 32 == 0;
+}
+
 hipError_t launch_ffn_gateup(const FfnGemmArgs& a, bool bf16, hipStream_t stream, bool counters_clear) {
   if (bf16) {
+    if (few_ok(a)) return launch_ffn_few(a, 0, stream);
     if (pp2_ok(a)) {
       int n_tt, n_ft;
       const GemmSplit sp = pp2_plan<0>(a, &n_tt, &n_ft);
@@ -1305,7 +1312,7 @@ inline bool down_on_pp2(const FfnGemmArgs& a, const GemmSplit& sp, int n_tt, int
 }
 
 int ffn_split_counters(const FfnGemmArgs& a, int mode, bool bf16) {
-  if (!bf16 || !pp2_ok(a) || !a.part || !a.tile_cnt) return 0;
+  if (!bf16 || !pp2_ok(a) || few_ok(a) || !a.part || !a.tile_cnt) return 0;
   int n_tt, n_ft;
   const GemmSplit sp = mode == 0 ? pp2_plan<0>(a, &n_tt, &n_ft) : pp2_plan<1>(a, &n_tt, &n_ft);
   if (mode == 1 && !down_on_pp2(a, sp, n_tt, n_ft)) return 0;
@@ -1321,8 +1328,10 @@ hipError_t launch_ffn_down_pruned(const FfnGemmArgs& a, hipStream_t stream, bool
 }
 
 int ffn_down_gap_slots(const FfnGemmArgs& a, bool bf16) {
-  int fpw;  // output features per wave of the kernel launch_ffn_down picks
-  if (bf16) {
+  int fpw;  // output features per slot of the kernel launch_ffn_down picks
+  if (bf16 && few_ok(a)) {
+    fpw = kFewGapFeatures;
+  } else if (bf16) {
     int n_tt, n_ft;
     const GemmSplit sp = pp2_plan<1>(a, &n_tt, &n_ft);
     if (down_on_pp2(a, sp, n_tt, n_ft)) fpw = 128;
@@ -1335,6 +1344,7 @@ int ffn_down_gap_slots(const FfnGemmArgs& a, bool bf16) {
 
 hipError_t launch_ffn_down(const FfnGemmArgs& a, bool bf16, hipStream_t stream, bool counters_clear) {
   if (bf16) {
+    if (few_ok(a)) return launch_ffn_few(a, 1, stream);
     int n_tt, n_ft;
     const GemmSplit sp = pp2_plan<1>(a, &n_tt, &n_ft);
     if (down_on_pp2(a, sp, n_tt, n_ft)) return launch_pp2<1, 8, true>(a, sp, n_tt, n_ft, stream, counters_clear);

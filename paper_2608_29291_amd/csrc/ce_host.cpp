@@ -195,9 +195,9 @@ WsLayout ws_layout(int which, int B, int T, int cap, int d, int d_ff, int elem) 
     L.seq_cnt = take(sB * 4);
   }
   if (which == CE_WS_BLOCK_GAP) {
-    // one slot per wave of the down GEMM and row; waves cover >= 32 features
+    // slots of the down GEMM per row; each covers >= 16 features
     const size_t sD = (size_t)(d < 0 ? 0 : d);
-    L.gap_part = take(sC * ((sD + 31) / 32) * 4 * sizeof(double));
+    L.gap_part = take(sC * ((sD + 15) / 16) * 4 * sizeof(double));
   }
   L.total = off;
   return L;

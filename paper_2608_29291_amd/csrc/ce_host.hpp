@@ -30,7 +30,7 @@ struct WsLayout {
   size_t gemm_part;  // float [slots x 256 x 256] K-piece partial sums of the FFN GEMMs' tail tiles
   size_t gu_cnt;     // int32 [kSplitMaxSlots] arrival counters of the gate/up tail tiles
   size_t dn_cnt;     // int32 [kSplitMaxSlots] arrival counters of the down tail tiles
-  size_t gap_part;   // double [cap x ceil(d / 32) x 4] layer-gap partial sums (CE_WS_BLOCK_GAP)
+  size_t gap_part;   // double [cap x ceil(d / 16) x 4] layer-gap partial sums (CE_WS_BLOCK_GAP)
   size_t row_seq;    // int32 [cap] sequence of each packed row (CE_WS_FFN_PRUNED)
   size_t sal_seg;    // float [tiles x kSalSegs x d_ff] per-segment |z| sums (CE_WS_FFN_PRUNED)
   size_t sal_meta;   // int32 [tiles x (kSalSegs + 1)] segment counts and sequences (CE_WS_FFN_PRUNED)

@@ -80,6 +80,12 @@ int ffn_split_counters(const FfnGemmArgs& a, int mode, bool bf16);
 hipError_t launch_ffn_down_pruned(const FfnGemmArgs& a, hipStream_t stream, bool counters_clear);
 bool ffn_pruned_ok(const FfnGemmArgs& gateup, const FfnGemmArgs& down);
 
+// FFN GEMMs for at most kFewRows packed rows (bf16, see ce_ffn_few.hip); mode
+// 0 = gate/up, 1 = down. No split counters, no pruning.
+constexpr int kFewRows = 64;
+constexpr int kFewGapFeatures = 16;  // features per layer-gap slot of its down kernel
+hipError_t launch_ffn_few(const FfnGemmArgs& a, int mode, hipStream_t stream);
+
 // Pruned FFN: row_seq[p] = b for the packed rows p of each sequence b.
 // Also zeroes seq_cnt [B] (the saliency kernel's arrival counters).
 hipError_t launch_row_seq(const int32_t* kept_offsets, int B, int cap, int32_t* row_seq, int32_t* seq_cnt,
