@@ -25,7 +25,7 @@ LIB_PATH = os.path.join(PKG, LIB_NAME)
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["ce_api.hip", "ce_score.hip", "ce_topk.hip", "ce_ffn.hip", "ce_ffn_few.hip", "ce_scatter.hip", "ce_stability.hip",
+SOURCES = ["ce_api.hip", "ce_score.hip", "ce_topk.hip", "ce_ffn.hip", "ce_ffn_few.hip", "ce_ffn_mid.hip", "ce_scatter.hip", "ce_stability.hip",
            "ce_ucs_ffn.hip", "ce_layer_gap.hip", "ce_attention.hip", "ce_attention_decode.hip", "ce_host.cpp"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"-I{INCLUDE}", f"-I{CSRC}"]

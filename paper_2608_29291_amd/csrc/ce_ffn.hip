@@ -313,21 +313,6 @@ __global__ __launch_bounds__(64 * kWW * kWT) void ffn_gemm_kernel(FfnGemmArgs a,
   }
 }
 
-// Token tiles of a gate/up launch over n packed rows: 256 rows each, except
-// that with `absorb` a last tile of at most 32 rows joins the tile before it
-// (which then holds 257 to 288 rows). A tile of a few rows would stream a
-// whole weight tile through LDS for them; the joined tile reads those rows'
-// fragments straight into registers while the weight superslabs it holds
-// anyway are in LDS (one more 32 x 32 block per wave). Non-decreasing in n,
-// and tiles(n0) + tiles(n1) <= tiles(n0 + n1) + 1, so a grid sized for the
-// capacity covers any packed count below it, split over two weight sets too.
-__host__ __device__ inline int gateup_token_tiles(int n, bool absorb) {
-  if (n <= 0) return 0;
-  int t = (n + 255) / 256;
-  if (absorb && t >= 2 && n - 256 * (t - 1) <= 32) --t;
-  return t;
-}
-
 // Ping-pong bf16 kernel (the gate/up workhorse, and the down GEMM on large
 // grids): 8 waves, two per SIMD, over a 256 x 256 tile. Wave w owns weight
 // rows 128 (w & 1) .. +128 and token rows 64 (w >> 1) .. +64 (4 x 2 MFMA
@@ -1286,15 +1271,27 @@ inline int64_t grid_tiles(const FfnGemmArgs& a, int feat_tile, int tok_tile) {
   return (int64_t)((a.cap + tok_tile - 1) / tok_tile + a.n_sets - 1) * ((a.n_feat + feat_tile - 1) / feat_tile);
 }
 
-// At most kFewRows rows without the pruning signal: the kernel that streams
-// each weight once past registers holding all rows.
+// At most kFewRows rows: the kernel that streams each weight once (faster at
+// every count up to there, 1.2 to 3 times; ce_ffn_few.hip).
 inline bool few_ok(const FfnGemmArgs& a) {
-  return a.cap <= kFewRows && !a.sal_part && !a.row_flag && pp2_ok(a) && a.n_feat % 32 == 0;
+  return a.cap <= kFewRows && pp2_ok(a) && a.n_feat % 32 == 0;
+}
+
+// The mid-size kernel's plan (use == 0: not taken).
+inline MidPlan mid_of(const FfnGemmArgs& a, int mode) {
+  MidPlan p = {0, 2, 0, 1};
+  if (a.cap > kFewRows && pp2_ok(a) && (mode == 0 || a.part))
+    p = mid_plan(mode, a.cap, a.n_feat, a.n_sets, a.k_bytes / 128);
+  return p;
 }
 
 hipError_t launch_ffn_gateup(const FfnGemmArgs& a, bool bf16, hipStream_t stream, bool counters_clear) {
   if (bf16) {
-    if (few_ok(a)) return launch_ffn_few(a, 0, stream);
+    const MidPlan mp = mid_of(a, 0);
+    if (few_ok(a) || mp.use) {
+      const hipError_t e = mp.use ? launch_ffn_mid(a, 0, mp, stream) : launch_ffn_few(a, 0, stream);
+      return e == hipSuccess && a.sal_part ? launch_segment_sums(a, stream) : e;
+    }
     if (pp2_ok(a)) {
       int n_tt, n_ft;
       const GemmSplit sp = pp2_plan<0>(a, &n_tt, &n_ft);
@@ -1312,7 +1309,7 @@ inline bool down_on_pp2(const FfnGemmArgs& a, const GemmSplit& sp, int n_tt, int
 }
 
 int ffn_split_counters(const FfnGemmArgs& a, int mode, bool bf16) {
-  if (!bf16 || !pp2_ok(a) || few_ok(a) || !a.part || !a.tile_cnt) return 0;
+  if (!bf16 || !pp2_ok(a) || few_ok(a) || mid_of(a, mode).use || !a.part || !a.tile_cnt) return 0;
   int n_tt, n_ft;
   const GemmSplit sp = mode == 0 ? pp2_plan<0>(a, &n_tt, &n_ft) : pp2_plan<1>(a, &n_tt, &n_ft);
   if (mode == 1 && !down_on_pp2(a, sp, n_tt, n_ft)) return 0;
@@ -1322,6 +1319,9 @@ int ffn_split_counters(const FfnGemmArgs& a, int mode, bool bf16) {
 bool ffn_pruned_ok(const FfnGemmArgs& g, const FfnGemmArgs& dn) { return pp2_ok(g) && pp2_ok(dn); }
 
 hipError_t launch_ffn_down_pruned(const FfnGemmArgs& a, hipStream_t stream, bool counters_clear) {
+  if (few_ok(a)) return launch_ffn_few(a, 1, stream);
+  const MidPlan mp = mid_of(a, 1);
+  if (mp.use) return launch_ffn_mid(a, 1, mp, stream);
   int n_tt, n_ft;
   const GemmSplit sp = pp2_plan<1>(a, &n_tt, &n_ft);
   return launch_pp2<1, 8, true, 2, true, true, true>(a, sp, n_tt, n_ft, stream, counters_clear);
@@ -1331,6 +1331,8 @@ int ffn_down_gap_slots(const FfnGemmArgs& a, bool bf16) {
   int fpw;  // output features per slot of the kernel launch_ffn_down picks
   if (bf16 && few_ok(a)) {
     fpw = kFewGapFeatures;
+  } else if (bf16 && mid_of(a, 1).use) {
+    fpw = a.n_feat;  // one slot per row
   } else if (bf16) {
     int n_tt, n_ft;
     const GemmSplit sp = pp2_plan<1>(a, &n_tt, &n_ft);
@@ -1345,6 +1347,8 @@ int ffn_down_gap_slots(const FfnGemmArgs& a, bool bf16) {
 hipError_t launch_ffn_down(const FfnGemmArgs& a, bool bf16, hipStream_t stream, bool counters_clear) {
   if (bf16) {
     if (few_ok(a)) return launch_ffn_few(a, 1, stream);
+    const MidPlan mp = mid_of(a, 1);
+    if (mp.use) return launch_ffn_mid(a, 1, mp, stream);
     int n_tt, n_ft;
     const GemmSplit sp = pp2_plan<1>(a, &n_tt, &n_ft);
     if (down_on_pp2(a, sp, n_tt, n_ft)) return launch_pp2<1, 8, true>(a, sp, n_tt, n_ft, stream, counters_clear);

@@ -48,6 +48,8 @@ __global__ __launch_bounds__(64 * kW) void ffn_few_kernel(FfnGemmArgs a) {
   static_assert(kW * kR * kNB * 1024 <= kW * kD * kStep, "the sums fit where the rings were");
 
   const int tid = threadIdx.x;
+  if (a.clear_cnt && blockIdx.x == 0 && blockIdx.y == 0)
+    for (int i = tid; i < a.clear_n; i += 64 * kW) a.clear_cnt[i] = 0;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int set = blockIdx.y;
@@ -84,13 +86,32 @@ __global__ __launch_bounds__(64 * kW) void ffn_few_kernel(FfnGemmArgs a) {
   const char* const w0 = set ? a.w0[1] : a.w0[0];
   const char* const w1 = set ? a.w1[1] : a.w1[0];
   const uint32_t w_bytes = (uint32_t)(a.n_feat * a.w_ld), t_bytes = (uint32_t)(a.tok_rows * a.tok_ld);
-  const int ns = a.k_bytes / kLine;
+  // pruned FFN (down): rows that run pruned read zeros from line ns_keep on, and
+  // K ends there when all rows do
+  int ns = a.k_bytes / kLine;
+  int keep = ns;
+  uint32_t cut[kNB][2];
+#pragma unroll
+  for (int n = 0; n < kNB; ++n) cut[n][0] = to[n][0], cut[n][1] = to[n][1];
+  if (kMode == 1 && a.row_flag) {
+    keep = min(ns, a.ns_keep);
+    auto flag = [&](int j) __attribute__((always_inline)) { return a.row_flag[a.omap1 ? a.omap1[j] : j] != 0; };
+#pragma unroll
+    for (int n = 0; n < kNB; ++n)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int j = row_lo + 16 * n + 8 * h + r8;
+        if (j < row_hi && flag(j)) cut[n][h] = 0x80000000u;
+      }
+    if (__ballot(row_lo + lane < row_hi && !flag(min(row_lo + lane, row_hi - 1))) == 0ull) ns = keep;
+  }
   char* const ring = smem + wave * (kD * kStep);
 
   // step s of this wave into ring slot d; past the last step an empty buffer
   // (zeros, no traffic) keeps the loop free of branches
   auto dma = [&](int s, int d) __attribute__((always_inline)) {
     const bool in = s < ns;
+    const bool tail = kMode == 1 && s >= keep;
     const __amdgpu_buffer_rsrc_t r0 = make_rsrc(w0, in ? w_bytes : 0u);
     const __amdgpu_buffer_rsrc_t r1 = make_rsrc(kMode == 0 ? w1 : w0, in ? w_bytes : 0u);
     const __amdgpu_buffer_rsrc_t rt = make_rsrc(a.tok, in ? t_bytes : 0u);
@@ -102,7 +123,7 @@ __global__ __launch_bounds__(64 * kW) void ffn_few_kernel(FfnGemmArgs a) {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             b >= kR ? rt : ((kMode == 0 && (b & 1)) ? r1 : r0),
             (__attribute__((address_space(3))) void*)(to_lds + b * kBlk + h * (kBlk / 2)), 16,
-            (int)(b >= kR ? to[b >= kR ? b - kR : 0][h] : wo[b < kR ? b : 0][h]), s * kLine, 0, 0);
+            (int)(b >= kR ? (tail ? cut : to)[b >= kR ? b - kR : 0][h] : wo[b < kR ? b : 0][h]), s * kLine, 0, 0);
   };
 
   f32x4_t acc[kR][kNB];

@@ -86,6 +86,59 @@ void gemm_items(int mode, int cap, int d, int d_ff, int n_sets, int elem, int64_
   *ns = (int)(k_bytes / 128);
 }
 
+// Both kernels' times in microseconds, fitted to launches of 65 to 4408 rows at
+// d, d_ff = 1536, 8960 and 3584, 18944 (within about 15%); only their order
+// matters. The mid-size kernel: rounds of 256 workgroups x stages (128 bytes
+// of K) x the stage time of its tile, or the weights' time from memory; down
+// adds the pieces' sums. The 256 x 256 kernel: gate/up by rounds; down, which
+// splits its tiles over K, with what its last-arriving workgroups add.
+MidPlan mid_plan(int mode, int cap, int n_feat, int n_sets, int ns) {
+  constexpr int kM[] = {2, 3, 4, 5, 6, 8};
+  constexpr double kT2[] = {0.35, 0.45, 0.58, 0.72, 0.80, 1.05};  // 128 weight rows
+  constexpr double kT4[] = {0.0, 0.85, 1.0, 1.15, 0.0, 0.0};      // 256 weight rows
+  constexpr int kCus = kXcdCount * kCusPerXcd;
+  const double mem = 3.0 + (mode == 0 ? 2.0 : 1.0) * n_feat * ns * 128.0 * n_sets / 4.2e6;
+  MidPlan best = {0, 2, 0, 1};
+  double cost = 1e30, best_c = 1e30;
+  for (int wb = 2; wb <= (mode == 0 ? 4 : 2); wb += 2)
+    for (int i = 0; i < 6; ++i) {
+      const double t = wb == 2 ? kT2[i] : kT4[i];
+      if (t == 0.0) continue;
+      const int ftile = mode == 0 ? 32 * wb : 64 * wb;
+      const int64_t tiles =
+          ((int64_t)(cap + 32 * kM[i] - 1) / (32 * kM[i]) + n_sets - 1) * ((n_feat + ftile - 1) / ftile);
+      for (int p = 1; p <= (mode == 0 ? 1 : kMidMaxPieces) && (p == 1 || 4 * p <= ns); ++p) {
+        const double rounds = (double)((tiles * p + kCus - 1) / kCus);
+        if (p > 1 && rounds > 2) break;
+        double c = 7.5 + rounds * ns / p * t;
+        const double tie = 0.05 * c;  // both bound by memory: the lighter loop
+        if (c < mem) c = mem;
+        if (mode == 1) c += 3.8 + (double)p * cap * n_feat * 4.0 / 6.5e6;
+        if (c + tie < cost) {
+          cost = c + tie;
+          best_c = c;
+          best.wb = wb;
+          best.m = kM[i];
+          best.pieces = p;
+        }
+      }
+    }
+  double big;
+  if (mode == 0) {
+    const int64_t items = (int64_t)(gateup_token_tiles(cap, true) + n_sets - 1) * ((n_feat + 127) / 128);
+    big = 8.0 + (double)((items + kCus - 1) / kCus) * ns * 1.4;
+    if (big < mem) big = mem;
+  } else {
+    const int64_t items = (int64_t)((cap + 255) / 256 + n_sets - 1) * ((n_feat + 255) / 256);
+    const GemmSplit sp = gemm_split(items, ns);
+    const int full = sp.whole_x / kCusPerXcd;  // full rounds before the split ones
+    big = sp.pieces > 1 ? 38.0 + 1.3 * (full * ns + (double)ns / sp.pieces) + 0.25 * (double)items
+                        : 8.0 + 1.3 * ns * (double)((items + kCus - 1) / kCus);
+  }
+  best.use = best_c < 0.88 * big;  // clearly, the fit being what it is
+  return best;
+}
+
 int score_token_tile(int B, int T, int d, int r_core, int r_exp, int elem) {
   const int r = r_core + (r_exp > 0 ? r_exp : 0);
   if (elem != 2 || B < 1 || T < 1 || d < 1 || r > 384) return 32;
@@ -179,8 +232,19 @@ WsLayout ws_layout(int which, int B, int T, int cap, int d, int d_ff, int elem) 
         const int n = kXcdCount * sp.tail_x * sp.pieces;
         slots = n > slots ? n : slots;
       }
-    if (slots > 0) {
-      L.gemm_part = take((size_t)slots * 256 * 256 * 4);
+    size_t part = (size_t)slots * 256 * 256 * 4;
+    // or the pieces' sums of the mid-size down kernel
+    for (int n_sets = 1; n_sets <= 2; ++n_sets) {
+      int64_t items;
+      int ns;
+      gemm_items(1, cap, d, d_ff, n_sets, elem, &items, &ns);
+      if (items == 0 || cap <= kFewRows) continue;
+      const MidPlan mp = mid_plan(1, cap, d, n_sets, ns);
+      const size_t n = mp.use ? (size_t)mp.pieces * sC * (size_t)d * 4 : 0;
+      part = n > part ? n : part;
+    }
+    if (part > 0) {
+      L.gemm_part = take(part);
       L.gu_cnt = take((size_t)kSplitMaxSlots * 4);
       L.dn_cnt = take((size_t)kSplitMaxSlots * 4);
     }

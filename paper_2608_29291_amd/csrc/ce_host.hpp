@@ -62,6 +62,21 @@ struct GemmSplit {
   int absorb;   // gate/up, whole tiles only: a last token tile of at most 32
                 // rows joins the tile before it (see gateup_token_tiles)
 };
+// Token tiles of a gate/up launch of the 256 x 256 kernel over n packed rows:
+// 256 rows each, except that with `absorb` a last tile of at most 32 rows joins
+// the tile before it (which then holds 257 to 288 rows). A tile of a few rows
+// would stream a whole weight tile through LDS for them; the joined tile reads
+// those rows' fragments straight into registers while the weight superslabs it
+// holds anyway are in LDS (one more 32 x 32 block per wave). Non-decreasing in
+// n, and tiles(n0) + tiles(n1) <= tiles(n0 + n1) + 1, so a grid sized for the
+// capacity covers any packed count below it, split over two weight sets too.
+// (constexpr: the kernels call it too.)
+constexpr int gateup_token_tiles(int n, bool absorb) {
+  if (n <= 0) return 0;
+  int t = (n + 255) / 256;
+  if (absorb && t >= 2 && n - 256 * (t - 1) <= 32) --t;
+  return t;
+}
 // Chosen by a cost model in units of one superslab's K-loop time: a whole
 // tile costs ns + 3.5 (prologue, epilogue); a piece ns / S + 2 (its partial
 // sums written) + the last arriver's reads (2.5 per partial tile read: one for
@@ -74,6 +89,20 @@ GemmSplit gemm_split(int64_t items, int ns);
 // when the ping-pong kernel does not apply (fp32, K not in whole 128-byte
 // superslabs, fewer than 3 of them, or 32-bit offsets overflowing).
 void gemm_items(int mode, int cap, int d, int d_ff, int n_sets, int elem, int64_t* items, int* ns);
+
+// Plan of a gate/up (mode 0) or down (mode 1) launch on the mid-size kernel
+// (ce_ffn_mid.hip): tiles of 64 wb weight rows x 32 m token rows, down in
+// `pieces` over K; use == 0 when the 256 x 256 kernel is expected to be faster.
+struct MidPlan {
+  int use;
+  int wb;
+  int m;
+  int pieces;
+};
+constexpr int kMidMaxPieces = 32;
+// At most this many packed rows run on the few-row kernel (ce_ffn_few.hip).
+constexpr int kFewRows = 64;
+MidPlan mid_plan(int mode, int cap, int n_feat, int n_sets, int ns);
 
 // Sequences per batch: some grids put the sequence index in their y dimension.
 constexpr int kMaxBatch = 65535;

@@ -75,21 +75,27 @@ hipError_t launch_ffn_down(const FfnGemmArgs& a, bool bf16, hipStream_t stream, 
 // Number of arrival counters a GEMM launch with these arguments uses (0: no
 // split); mode 0 = gate/up, 1 = down.
 int ffn_split_counters(const FfnGemmArgs& a, int mode, bool bf16);
-// Down GEMM of the pruned FFN: always the ping-pong kernel (the pruning
-// logic lives there); the caller checks ffn_pruned_ok first.
+// Down GEMM of the pruned FFN, with the same choice of kernel; the caller
+// checks ffn_pruned_ok first.
 hipError_t launch_ffn_down_pruned(const FfnGemmArgs& a, hipStream_t stream, bool counters_clear);
 bool ffn_pruned_ok(const FfnGemmArgs& gateup, const FfnGemmArgs& down);
 
 // FFN GEMMs for at most kFewRows packed rows (bf16, see ce_ffn_few.hip); mode
 // 0 = gate/up, 1 = down. No split counters, no pruning.
-constexpr int kFewRows = 64;
 constexpr int kFewGapFeatures = 16;  // features per layer-gap slot of its down kernel
 hipError_t launch_ffn_few(const FfnGemmArgs& a, int mode, hipStream_t stream);
+
+// The same for mid-size packed counts (ce_ffn_mid.hip); down: a.part holds
+// pieces x cap x n_feat floats, one layer-gap slot per row.
+hipError_t launch_ffn_mid(const FfnGemmArgs& a, int mode, const MidPlan& p, hipStream_t stream);
 
 // Pruned FFN: row_seq[p] = b for the packed rows p of each sequence b.
 // Also zeroes seq_cnt [B] (the saliency kernel's arrival counters).
 hipError_t launch_row_seq(const int32_t* kept_offsets, int B, int cap, int32_t* row_seq, int32_t* seq_cnt,
                           hipStream_t stream);
+// sal_part and sal_meta of a gate/up launch from its activations (a.out), for
+// the kernels whose epilogue does not form them.
+hipError_t launch_segment_sums(const FfnGemmArgs& gateup, hipStream_t stream);
 // Saliency (Eq. 8) of each sequence from the gate/up epilogue's segment sums
 // (falling back to act for tiles with more than kSalSegs segments) and the
 // leakage (Eq. 9) of the tail channels [n_keep, d_ff); use_pruned = leakage <= delta,

@@ -274,6 +274,90 @@ struct SegSalArgs {
   uint8_t* row_flag;
 };
 
+// Per 256-row token tile and run of rows of one sequence (a segment), the sums
+// of |z| per channel, as the 256 x 256 gate/up kernel's epilogue forms them: a
+// workgroup takes 128 channels of a tile, a thread 8 channels of the rows of
+// one of 16 classes, all loaded at once; the classes are added in a fixed
+// order (lanes 16 and 32 apart, then the waves). Bound: one read of act, a few
+// MB at the packed counts that come here; 4 us of latencies.
+__global__ __launch_bounds__(256) void segment_sums_kernel(FfnGemmArgs a) {
+  __shared__ int keys[256];
+  __shared__ int seg[kSalSegs + 1];
+  __shared__ int wcnt[4];
+  __shared__ float red[2][4][128];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tt = blockIdx.y;
+  int kt = *a.kt_ptr;
+  kt = kt < 0 ? 0 : (kt > a.cap ? a.cap : kt);
+  int n0 = kt;
+  if (a.n_sets == 2 && a.n0_ptr) {
+    n0 = *a.n0_ptr;
+    n0 = n0 < 0 ? 0 : (n0 > kt ? kt : n0);
+  }
+  const int tiles0 = (n0 + 255) / 256;
+  const int lo = tt < tiles0 ? tt * 256 : n0 + (tt - tiles0) * 256;
+  const int hi = min(lo + 256, tt < tiles0 ? n0 : kt);
+  if (lo >= hi) return;
+  const int rows = hi - lo;
+  const int rg = 4 * wave + (lane >> 4);  // row class: rows rg, rg + 16, ...
+  const int c0 = blockIdx.x * 128 + 8 * (lane & 15);
+  uint4 v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int r = min(rg + 16 * i, rows - 1);
+    v[i] = *reinterpret_cast<const uint4*>(a.out + (int64_t)(lo + r) * a.out_ld +
+                                           (int64_t)min(c0, a.n_feat - 8) * 2);
+  }
+  const int j = lo + tid;
+  const int key = tid < rows ? a.row_seq[a.map1 ? a.map1[j] : j] : -1;
+  keys[tid] = key;
+  __syncthreads();
+  const bool st = tid < rows && (tid == 0 || keys[tid - 1] != key);
+  const uint64_t sm = __ballot(st);
+  if (lane == 0) wcnt[wave] = __popcll(sm);
+  __syncthreads();
+  int k0 = __popcll(sm & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
+  for (int w = 0; w < wave; ++w) k0 += wcnt[w];
+  if (st && k0 < kSalSegs) seg[k0] = tid;
+  const int nseg = (wcnt[0] + wcnt[1]) + (wcnt[2] + wcnt[3]);
+  __syncthreads();
+  if (blockIdx.x == 0 && tid <= kSalSegs) {
+    int32_t* const meta = a.sal_meta + (int64_t)tt * (kSalSegs + 1);
+    if (tid == 0) meta[0] = nseg;
+    else if (tid - 1 < nseg) meta[tid] = keys[seg[tid - 1]];
+  }
+  if (nseg > kSalSegs) return;
+  for (int k = 0; k < nseg; ++k) {
+    const int r0 = seg[k], r1 = k + 1 < nseg ? seg[k + 1] : rows;
+    float sum[8] = {};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int r = rg + 16 * i;
+      const uint32_t in = r >= r0 && r < r1 ? 0xffffffffu : 0u;
+      const uint32_t x[4] = {v[i].x & in, v[i].y & in, v[i].z & in, v[i].w & in};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        sum[2 * e] += fabsf(__uint_as_float(x[e] << 16));
+        sum[2 * e + 1] += fabsf(__uint_as_float(x[e] & 0xffff0000u));
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      sum[e] += __shfl_xor(sum[e], 16);
+      sum[e] += __shfl_xor(sum[e], 32);
+    }
+    if (lane < 16) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) red[k & 1][wave][8 * lane + e] = sum[e];
+    }
+    __syncthreads();  // (two buffers: one barrier per segment)
+    const int c = blockIdx.x * 128 + tid;
+    if (tid < 128 && c < a.n_feat)
+      a.sal_part[((int64_t)tt * kSalSegs + k) * a.n_feat + c] =
+          (red[k & 1][0][tid] + red[k & 1][1][tid]) + (red[k & 1][2][tid] + red[k & 1][3][tid]);
+  }
+}
+
 constexpr int kMetaTiles = 64;  // token tiles whose segment lists are staged in LDS at a time
 
 __global__ __launch_bounds__(256) void saliency_seg_kernel(SegSalArgs a) {
@@ -416,6 +500,12 @@ __global__ __launch_bounds__(256) void saliency_seg_kernel(SegSalArgs a) {
 hipError_t launch_row_seq(const int32_t* kept_offsets, int B, int cap, int32_t* row_seq, int32_t* seq_cnt,
                           hipStream_t stream) {
   hipLaunchKernelGGL(row_seq_kernel, dim3(B), dim3(256), 0, stream, kept_offsets, cap, row_seq, seq_cnt);
+  return hipGetLastError();
+}
+
+hipError_t launch_segment_sums(const FfnGemmArgs& g, hipStream_t stream) {
+  const int tiles = (g.cap + 255) / 256 + (g.n_sets - 1);
+  hipLaunchKernelGGL(segment_sums_kernel, dim3((g.n_feat + 127) / 128, tiles), dim3(256), 0, stream, g);
   return hipGetLastError();
 }
 
