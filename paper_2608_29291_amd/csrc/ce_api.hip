@@ -290,9 +290,15 @@ int routed_block_impl(const ce_batch* batch, const void* hidden_in, void* hidden
   sel.clear_n = gu_counters;
   CE_TRY(launch_select(sel, s));
   // bypass path for a separate output buffer: dropped rows copied unchanged
-  if (hidden_in != hidden_out)
-    CE_TRY(launch_copy_rows(static_cast<const char*>(hidden_in), static_cast<char*>(hidden_out),
-                            (int64_t)ffn->d * elem, batch->T, token_pos, s));
+  if (hidden_in != hidden_out) {
+    const int blocks = (batch->T + kCopyRows - 1) / kCopyRows;
+    const BypassCopy copy{static_cast<const char*>(hidden_in), static_cast<char*>(hidden_out),
+                          (int64_t)ffn->d * elem, batch->T, token_pos, blocks < 1024 ? blocks : 1024, 0};
+    if (batch->kept_capacity > 0 && gateup_takes_copy(g, bf16))
+      g.copy = copy;
+    else
+      CE_TRY(launch_copy_rows(copy.src, copy.dst, copy.row_bytes, batch->T, token_pos, s));
+  }
   // layer gap (Eq. 7) from the down GEMM's per-row sums, after the block
   auto finish_gap = [&]() -> int {
     if (!go) return CE_OK;

@@ -155,6 +155,39 @@ __device__ __forceinline__ f32x4_t load4(const char* p) {
   return r;
 }
 
+// Workgroup `blk` of `blocks` copies the rows with token_pos[i] < 0: 32 rows at
+// a time, four per wave and step with their loads in flight together (kWaves
+// waves; row_bytes a multiple of 16).
+template <int kWaves>
+__device__ __forceinline__ void copy_bypass_rows(const char* __restrict__ src, char* __restrict__ dst,
+                                                 int64_t row_bytes, int T, const int32_t* __restrict__ token_pos,
+                                                 int blk, int blocks) {
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  for (int base = blk * 32; base < T; base += blocks * 32)
+    for (int g = wave; g < 8; g += kWaves) {
+      bool go[4];
+      const char* s[4];
+      char* d[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = base + 4 * g + i;
+        go[i] = r < T && token_pos[r < T ? r : 0] < 0;
+        s[i] = src + (int64_t)(r < T ? r : 0) * row_bytes;
+        d[i] = dst + (int64_t)(r < T ? r : 0) * row_bytes;
+      }
+      for (int64_t o = lane * 16; o < row_bytes; o += 64 * 16) {
+        u32x4_t v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (go[i]) v[i] = *reinterpret_cast<const u32x4_t*>(s[i] + o);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (go[i]) *reinterpret_cast<u32x4_t*>(d[i] + o) = v[i];
+      }
+    }
+}
+
 // Order-preserving uint32 key of a float32 logit: larger logit -> larger key;
 // -0 and +0 share a key; every NaN maps to 0, below -inf (0x007fffff).
 __device__ __forceinline__ uint32_t logit_key(float x) {

@@ -62,6 +62,11 @@ __global__ __launch_bounds__(64 * kWW * kWT) void ffn_gemm_kernel(FfnGemmArgs a,
   constexpr int kTLoads = kTR / kRowsPerPass;
   static_assert(kWLoads * kRowsPerPass == kWR && kTLoads * kRowsPerPass == kTR, "tile / threads");
   static_assert(kMode == 1 || (kRowsPerPass % 32) == 0 || (32 % kRowsPerPass) == 0, "pass rows");
+  if (kMode == 0 && (int)blockIdx.x >= a.copy.first) {
+    copy_bypass_rows<kWW * kWT>(a.copy.src, a.copy.dst, a.copy.row_bytes, a.copy.T, a.copy.token_pos,
+                                (int)blockIdx.x - a.copy.first, a.copy.blocks);
+    return;
+  }
   if (a.clear_cnt && blockIdx.x == 0)
     for (int i = threadIdx.x; i < a.clear_n; i += kThreads) a.clear_cnt[i] = 0;
   constexpr int kStage = (kWR + kTR) * kKB;
@@ -1238,13 +1243,13 @@ inline bool pp2_ok(const FfnGemmArgs& a) { return big_ok(a) && a.k_bytes % 128 =
 
 template <bool kBF16, int kMode, int kWR, int kTR, int kWW, int kWT, int kStages, int kPf = 1,
           int kGroup = 1>
-hipError_t launch_cfg(const FfnGemmArgs& a, hipStream_t stream) {
+hipError_t launch_cfg(FfnGemmArgs a, hipStream_t stream) {
   constexpr int kFTile = (kMode == 0) ? kWR / 2 : kWR;
   const int n_tt = (a.cap + kTR - 1) / kTR + (a.n_sets - 1);
   const int n_ft = (a.n_feat + kFTile - 1) / kFTile;
   if (n_tt <= 0 || n_ft <= 0) return hipSuccess;
   const int total = n_tt * n_ft;
-  const int grid = ((total + kXcds - 1) / kXcds) * kXcds;
+  const int grid = grid_with_copy(a.copy, ((total + kXcds - 1) / kXcds) * kXcds);
   hipLaunchKernelGGL((ffn_gemm_kernel<kBF16, kMode, kWR, kTR, kWW, kWT, kStages, kPf, kGroup>), dim3(grid),
                      dim3(64 * kWW * kWT), 0, stream, a, n_tt, n_ft);
   return hipGetLastError();
@@ -1314,6 +1319,10 @@ int ffn_split_counters(const FfnGemmArgs& a, int mode, bool bf16) {
   const GemmSplit sp = mode == 0 ? pp2_plan<0>(a, &n_tt, &n_ft) : pp2_plan<1>(a, &n_tt, &n_ft);
   if (mode == 1 && !down_on_pp2(a, sp, n_tt, n_ft)) return 0;
   return sp.pieces > 1 ? kXcds * sp.tail_x : 0;
+}
+
+bool gateup_takes_copy(const FfnGemmArgs& g, bool bf16) {
+  return !bf16 || !pp2_ok(g) || few_ok(g) || mid_of(g, 0).use;
 }
 
 bool ffn_pruned_ok(const FfnGemmArgs& g, const FfnGemmArgs& dn) { return pp2_ok(g) && pp2_ok(dn); }

@@ -48,6 +48,12 @@ __global__ __launch_bounds__(64 * kW) void ffn_few_kernel(FfnGemmArgs a) {
   static_assert(kW * kR * kNB * 1024 <= kW * kD * kStep, "the sums fit where the rings were");
 
   const int tid = threadIdx.x;
+  if (kMode == 0 && (int)blockIdx.x >= a.copy.first) {
+    if (blockIdx.y == 0)
+      copy_bypass_rows<kW>(a.copy.src, a.copy.dst, a.copy.row_bytes, a.copy.T, a.copy.token_pos,
+                           (int)blockIdx.x - a.copy.first, a.copy.blocks);
+    return;
+  }
   if (a.clear_cnt && blockIdx.x == 0 && blockIdx.y == 0)
     for (int i = tid; i < a.clear_n; i += 64 * kW) a.clear_cnt[i] = 0;
   const int lane = tid & 63;
@@ -242,9 +248,9 @@ __global__ __launch_bounds__(64 * kW) void ffn_few_kernel(FfnGemmArgs a) {
 }
 
 template <int kMode, int kF, int kNB, int kW, int kD>
-hipError_t launch_few(const FfnGemmArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL((ffn_few_kernel<kMode, kF, kNB, kW, kD>), dim3(a.n_feat / (16 * kF), a.n_sets), dim3(64 * kW), 0,
-                     stream, a);
+hipError_t launch_few(FfnGemmArgs a, hipStream_t stream) {
+  const int grid = grid_with_copy(a.copy, a.n_feat / (16 * kF));
+  hipLaunchKernelGGL((ffn_few_kernel<kMode, kF, kNB, kW, kD>), dim3(grid, a.n_sets), dim3(64 * kW), 0, stream, a);
   return hipGetLastError();
 }
 

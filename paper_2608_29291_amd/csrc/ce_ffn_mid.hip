@@ -62,6 +62,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __shared__ __attribute__((aligned(1024))) char smem[kSlots * kStage];
 
   const int tid = threadIdx.x;
+  if (kMode == 0 && (int)blockIdx.x >= a.copy.first) {
+    copy_bypass_rows<8>(a.copy.src, a.copy.dst, a.copy.row_bytes, a.copy.T, a.copy.token_pos,
+                        (int)blockIdx.x - a.copy.first, a.copy.blocks);
+    return;
+  }
   if (a.clear_cnt && blockIdx.x == 0)
     for (int i = tid; i < a.clear_n; i += 512) a.clear_cnt[i] = 0;
   const int lane = tid & 63;
@@ -368,11 +373,11 @@ __global__ __launch_bounds__(256) void ffn_mid_add_kernel(FfnGemmArgs a, int pie
 }
 
 template <int kMode, int kWB, int kM>
-hipError_t launch_mid(const FfnGemmArgs& a, int pieces, hipStream_t stream) {
+hipError_t launch_mid(FfnGemmArgs a, int pieces, hipStream_t stream) {
   constexpr int kFT = kMode == 0 ? 32 * kWB : 64 * kWB;
   const int n_tt = (a.cap + 32 * kM - 1) / (32 * kM) + (a.n_sets - 1);
   const int n_ft = (a.n_feat + kFT - 1) / kFT;
-  const int grid = (n_tt * n_ft * pieces + kXcdCount - 1) / kXcdCount * kXcdCount;
+  const int grid = grid_with_copy(a.copy, (n_tt * n_ft * pieces + kXcdCount - 1) / kXcdCount * kXcdCount);
   hipLaunchKernelGGL((ffn_mid_kernel<kMode, kWB, kM>), dim3(grid), dim3(512), 0, stream, a, n_tt, n_ft, pieces);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || kMode == 0) return e;

@@ -8,6 +8,26 @@
 
 namespace ce {
 
+// Rows that bypass the block (token_pos[i] < 0), copied from src to dst when
+// the output is a buffer of its own. The gate/up launch carries them in extra
+// workgroups after its own, where that costs less than a launch of their own
+// (gateup_takes_copy).
+struct BypassCopy {
+  const char* src;  // NULL: none
+  char* dst;
+  int64_t row_bytes;  // a multiple of 16
+  int T;
+  const int32_t* token_pos;
+  int blocks;  // extra workgroups
+  int first;   // index of the first of them (set by the launcher)
+};
+constexpr int kCopyRows = 32;  // rows of one such workgroup at a time
+// The grid of a launch of n workgroups with its bypass copy behind it.
+inline int grid_with_copy(BypassCopy& c, int n) {
+  c.first = n;
+  return n + (c.src ? c.blocks : 0);
+}
+
 // One "weights x tokens" FFN GEMM (see ce_ffn.hip).
 struct FfnGemmArgs {
   // weights: rows = output features, K-contiguous; per set.
@@ -65,6 +85,7 @@ struct FfnGemmArgs {
   int32_t* sal_meta;
   const uint8_t* row_flag;
   int ns_keep;
+  BypassCopy copy;
 };
 
 // counters_clear: this launch's arrival counters (tile_cnt) were already
@@ -72,6 +93,12 @@ struct FfnGemmArgs {
 // fill kernel clears them first when the launch splits.
 hipError_t launch_ffn_gateup(const FfnGemmArgs& a, bool bf16, hipStream_t stream, bool counters_clear = false);
 hipError_t launch_ffn_down(const FfnGemmArgs& a, bool bf16, hipStream_t stream, bool counters_clear = false);
+// Whether the gate/up launch takes the bypass copy: when it is not the 256 x
+// 256 kernel, that is on small batches, where a launch of its own is mostly
+// start-up (2.4 to 5 us of 61 to 95 us per block). Behind the 256 x 256 tiles,
+// on the CUs of their last round, the copy held up the tiles there (370 -> 375
+// us per block at the Show-o2 understanding shape).
+bool gateup_takes_copy(const FfnGemmArgs& gateup, bool bf16);
 // Number of arrival counters a GEMM launch with these arguments uses (0: no
 // split); mode 0 = gate/up, 1 = down.
 int ffn_split_counters(const FfnGemmArgs& a, int mode, bool bf16);
