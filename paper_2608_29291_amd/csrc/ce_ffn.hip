@@ -1269,9 +1269,10 @@ hipError_t launch_cfg(FfnGemmArgs a, hipStream_t stream) {
 // (GemmSplit) when the workspace holds the partial sums: 3108 gate/up tiles at
 // the 7B width are 12 full rounds plus 36 tiles, 294 down tiles one round plus
 // 38, the 108 down tiles of the understanding workload less than one round.
-// fp32 data (tiny workloads) uses 128 x 128 tiles, or smaller ones when those
-// would leave most of the chip idle (fp32 MFMAs run at 1/16 of the bf16 rate,
-// so a handful of large tiles would each take tens of microseconds).
+// fp32 data uses 128 x 128 tiles, or the K-split kernel of ce_ffn_few.hip when
+// those would leave most of the chip idle (few32_ok: fp32 MFMAs run at 1/16 of
+// the bf16 rate, so a handful of large tiles would each take tens of
+// microseconds), and 32 x 32 ones for a narrow down product over many rows.
 inline int64_t grid_tiles(const FfnGemmArgs& a, int feat_tile, int tok_tile) {
   return (int64_t)((a.cap + tok_tile - 1) / tok_tile + a.n_sets - 1) * ((a.n_feat + feat_tile - 1) / feat_tile);
 }
@@ -1280,6 +1281,19 @@ inline int64_t grid_tiles(const FfnGemmArgs& a, int feat_tile, int tok_tile) {
 // every count up to there, 1.2 to 3 times; ce_ffn_few.hip).
 inline bool few_ok(const FfnGemmArgs& a) {
   return a.cap <= kFewRows && pp2_ok(a) && a.n_feat % 32 == 0;
+}
+
+// fp32: the same kernel with row tiles, where the tiles of ffn_gemm_kernel are
+// too few to hide a tile's chain of products over K. Gate/up up to 256 rows or
+// fewer than 128 tiles of 64 features x 128 rows; down up to 1024 rows and
+// fewer than 128 tiles of 128 x 128. Measured, us, this and the tiles: d 256,
+// d_ff 1024, gate/up 160 rows 7.6 and 14.6, 700 rows 18 and 23, 1500 rows 32
+// and 27; down 160 rows 5.6 and 26, 700 rows 13 and 27, 1500 rows 27 and 27;
+// d 1536, d_ff 8960, gate/up 128 rows 82 and 119, 256 rows 164 and 204, 512
+// rows 326 and 319; down 128 rows 56 and 201, 512 rows 206 and 223.
+inline bool few32_ok(const FfnGemmArgs& a, int mode) {
+  if (!big_ok(a)) return false;
+  return mode == 0 ? a.cap <= 256 || grid_tiles(a, 64, 128) < 128 : a.cap <= 1024 && grid_tiles(a, 128, 128) < 128;
 }
 
 // The mid-size kernel's plan (use == 0: not taken).
@@ -1294,7 +1308,7 @@ hipError_t launch_ffn_gateup(const FfnGemmArgs& a, bool bf16, hipStream_t stream
   if (bf16) {
     const MidPlan mp = mid_of(a, 0);
     if (few_ok(a) || mp.use) {
-      const hipError_t e = mp.use ? launch_ffn_mid(a, 0, mp, stream) : launch_ffn_few(a, 0, stream);
+      const hipError_t e = mp.use ? launch_ffn_mid(a, 0, mp, stream) : launch_ffn_few(a, 0, true, stream);
       return e == hipSuccess && a.sal_part ? launch_segment_sums(a, stream) : e;
     }
     if (pp2_ok(a)) {
@@ -1304,7 +1318,8 @@ hipError_t launch_ffn_gateup(const FfnGemmArgs& a, bool bf16, hipStream_t stream
     }
     return launch_cfg<true, 0, 256, 256, 4, 2, 1, 1, 4>(a, stream);
   }
-  if (grid_tiles(a, 64, 128) < 128) return launch_cfg<false, 0, 64, 64, 1, 2, 2>(a, stream);
+  if (few32_ok(a, 0)) return launch_ffn_few(a, 0, false, stream);
+  if (!big_ok(a) && grid_tiles(a, 64, 128) < 128) return launch_cfg<false, 0, 64, 64, 1, 2, 2>(a, stream);
   return launch_cfg<false, 0, 128, 128, 2, 2, 2>(a, stream);
 }
 
@@ -1328,7 +1343,7 @@ bool gateup_takes_copy(const FfnGemmArgs& g, bool bf16) {
 bool ffn_pruned_ok(const FfnGemmArgs& g, const FfnGemmArgs& dn) { return pp2_ok(g) && pp2_ok(dn); }
 
 hipError_t launch_ffn_down_pruned(const FfnGemmArgs& a, hipStream_t stream, bool counters_clear) {
-  if (few_ok(a)) return launch_ffn_few(a, 1, stream);
+  if (few_ok(a)) return launch_ffn_few(a, 1, true, stream);
   const MidPlan mp = mid_of(a, 1);
   if (mp.use) return launch_ffn_mid(a, 1, mp, stream);
   int n_tt, n_ft;
@@ -1348,14 +1363,14 @@ int ffn_down_gap_slots(const FfnGemmArgs& a, bool bf16) {
     if (down_on_pp2(a, sp, n_tt, n_ft)) fpw = 128;
     else fpw = 64;  // 256 x 128 tiles on 4 x 2 waves, 128 x 128 on 2 x 2
   } else {
-    fpw = grid_tiles(a, 128, 128) < 128 ? 32 : 64;
+    fpw = few32_ok(a, 1) ? kFewGapFeatures : grid_tiles(a, 128, 128) < 128 ? 32 : 64;
   }
   return (a.n_feat + fpw - 1) / fpw;
 }
 
 hipError_t launch_ffn_down(const FfnGemmArgs& a, bool bf16, hipStream_t stream, bool counters_clear) {
   if (bf16) {
-    if (few_ok(a)) return launch_ffn_few(a, 1, stream);
+    if (few_ok(a)) return launch_ffn_few(a, 1, true, stream);
     const MidPlan mp = mid_of(a, 1);
     if (mp.use) return launch_ffn_mid(a, 1, mp, stream);
     int n_tt, n_ft;
@@ -1364,6 +1379,7 @@ hipError_t launch_ffn_down(const FfnGemmArgs& a, bool bf16, hipStream_t stream, 
     if (a.n_feat < 3072) return launch_cfg<true, 1, 256, 128, 4, 2, 2, 1, 64>(a, stream);
     return launch_cfg<true, 1, 128, 128, 2, 2, 2, 1, 64>(a, stream);
   }
+  if (few32_ok(a, 1)) return launch_ffn_few(a, 1, false, stream);
   if (grid_tiles(a, 128, 128) < 128) return launch_cfg<false, 1, 32, 32, 1, 1, 2>(a, stream);
   return launch_cfg<false, 1, 128, 128, 2, 2, 2>(a, stream);
 }

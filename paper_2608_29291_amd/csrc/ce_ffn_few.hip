@@ -1,6 +1,6 @@
 // SwiGLU FFN GEMMs for few packed rows (decode steps: one token per running
-// request), bf16: the same gate/up and down products as ce_ffn.hip with the
-// same row maps and epilogues.
+// request; small fp32 batches, in tiles of 16 or 32 rows): the same gate/up and
+// down products as ce_ffn.hip with the same row maps and epilogues.
 //
 // Bound: the weights, each read once. A 256 x 256 tile kernel streams 256
 // token rows through LDS for a handful of rows and fills a fraction of the
@@ -30,6 +30,20 @@ namespace {
 constexpr int kLine = 128;  // bytes of K per step of a wave: two 16x16x32 MFMAs
 constexpr int kBlk = 16 * kLine;  // one block of 16 rows in LDS
 
+// One 16-byte chunk per lane of both operands on a 16 x 16 block: lane l holds
+// chunk l / 16 of row l % 16 (bf16: K = 32; fp32: four products of K = 4).
+template <bool kBF16>
+__device__ __forceinline__ void mfma16_step(f32x4_t& acc, const u32x4_t& a, const u32x4_t& b) {
+  if constexpr (kBF16) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
+                                                  acc, 0, 0, 0);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]), acc, 0, 0, 0);
+  }
+}
+
 __device__ __forceinline__ int map_row(int j, const int32_t* m1, const int32_t* m2) {
   const int r = m1 ? m1[j] : j;
   return m2 ? m2[r] : r;
@@ -38,7 +52,7 @@ __device__ __forceinline__ int map_row(int j, const int32_t* m1, const int32_t* 
 // kMode 0: gate/up + SwiGLU over kF blocks of 16 features (blocks 2i: gate,
 // 2i + 1: up); 1: down (+ residual, layer-gap sums) over one block.
 // kNB: blocks of 16 token rows. kW waves, each with a ring of kD steps.
-template <int kMode, int kF, int kNB, int kW, int kD>
+template <bool kBF16, int kMode, int kF, int kNB, int kW, int kD>
 __global__ __launch_bounds__(64 * kW) void ffn_few_kernel(FfnGemmArgs a) {
   constexpr int kR = kMode == 0 ? 2 * kF : kF;  // blocks of 16 weight rows
   static_assert(kMode == 0 || kF == 1, "down: one block of features");
@@ -49,12 +63,12 @@ __global__ __launch_bounds__(64 * kW) void ffn_few_kernel(FfnGemmArgs a) {
 
   const int tid = threadIdx.x;
   if (kMode == 0 && (int)blockIdx.x >= a.copy.first) {
-    if (blockIdx.y == 0)
+    if (blockIdx.y == 0 && blockIdx.z == 0)
       copy_bypass_rows<kW>(a.copy.src, a.copy.dst, a.copy.row_bytes, a.copy.T, a.copy.token_pos,
                            (int)blockIdx.x - a.copy.first, a.copy.blocks);
     return;
   }
-  if (a.clear_cnt && blockIdx.x == 0 && blockIdx.y == 0)
+  if (a.clear_cnt && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
     for (int i = tid; i < a.clear_n; i += 64 * kW) a.clear_cnt[i] = 0;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -65,7 +79,9 @@ __global__ __launch_bounds__(64 * kW) void ffn_few_kernel(FfnGemmArgs a) {
   int n0 = *(two_sets ? a.n0_ptr : a.kt_ptr);
   kt = kt < 0 ? 0 : (kt > a.cap ? a.cap : kt);
   n0 = two_sets ? (n0 < 0 ? 0 : (n0 > kt ? kt : n0)) : kt;
-  const int row_lo = set ? n0 : 0, row_hi = set ? kt : n0;
+  constexpr int kElem = kBF16 ? 2 : 4;
+  const int row_lo = (set ? n0 : 0) + (int)blockIdx.z * (16 * kNB);
+  const int row_hi = min(row_lo + 16 * kNB, set ? kt : n0);
   if (row_lo >= row_hi) return;
 
   // ---- DMA plan: an instruction moves 8 rows x 128 bytes, whole lines; lane
@@ -167,9 +183,7 @@ __global__ __launch_bounds__(64 * kW) void ffn_few_kernel(FfnGemmArgs a) {
         for (int r = 0; r < kR; ++r)
 #pragma unroll
           for (int n = 0; n < kNB; ++n)
-            acc[r][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, f[h][r]),
-                                                                __builtin_bit_cast(bf16x8_t, f[h][kR + n]), acc[r][n],
-                                                                0, 0, 0);
+            mfma16_step<kBF16>(acc[r][n], f[h][r], f[h][kR + n]);
       // every fragment is in registers: the slot takes the step kD ahead
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
@@ -201,24 +215,27 @@ __global__ __launch_bounds__(64 * kW) void ffn_few_kernel(FfnGemmArgs a) {
     if constexpr (kMode == 0) {
       const f32x4_t g = total(2 * i * kNB + n), up = total((2 * i + 1) * kNB + n);
       if (jr < row_hi)
-        store4<true>(a.out + (int64_t)map_row(jr, a.omap1, a.omap2) * a.out_ld + (int64_t)f * 2,
-                     silu_f32(g.x) * up.x, silu_f32(g.y) * up.y, silu_f32(g.z) * up.z, silu_f32(g.w) * up.w);
+        store4<kBF16>(a.out + (int64_t)map_row(jr, a.omap1, a.omap2) * a.out_ld + (int64_t)f * kElem,
+                      silu_f32(g.x) * up.x, silu_f32(g.y) * up.y, silu_f32(g.z) * up.z, silu_f32(g.w) * up.w);
     } else {
       f32x4_t v = total(n);
       const bool in = jr < row_hi;
       double gdot = 0.0, gin = 0.0, gout = 0.0;  // layer-gap sums over this lane's features
       if (in) {
         const int64_t oi = map_row(jr, a.omap1, a.omap2);
-        char* const orow = a.out + oi * a.out_ld + (int64_t)f * 2;
+        char* const orow = a.out + oi * a.out_ld + (int64_t)f * kElem;
         f32x4_t res = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (a.res) res = load4<true>(a.res + oi * a.res_ld + (int64_t)f * 2);
+        if (a.res) res = load4<kBF16>(a.res + oi * a.res_ld + (int64_t)f * kElem);
         v += res;
-        const u32x2_t pk = {pack_bf16(v.x, v.y), pack_bf16(v.z, v.w)};
-        *reinterpret_cast<u32x2_t*>(orow) = pk;
+        store4<kBF16>(orow, v.x, v.y, v.z, v.w);
         if (a.gap_part) {
-          // the values as stored, after the one rounding
-          const float y[4] = {bf16_to_f32(pk.x & 0xffffu), bf16_to_f32(pk.x >> 16), bf16_to_f32(pk.y & 0xffffu),
-                              bf16_to_f32(pk.y >> 16)};
+          // the values as stored (bf16: after the one rounding)
+          float y[4] = {v.x, v.y, v.z, v.w};
+          if constexpr (kBF16) {
+            const u32x2_t pk = {pack_bf16(v.x, v.y), pack_bf16(v.z, v.w)};
+            y[0] = bf16_to_f32(pk.x & 0xffffu), y[1] = bf16_to_f32(pk.x >> 16);
+            y[2] = bf16_to_f32(pk.y & 0xffffu), y[3] = bf16_to_f32(pk.y >> 16);
+          }
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             gdot = fma((double)res[e], (double)y[e], gdot);
@@ -247,24 +264,25 @@ __global__ __launch_bounds__(64 * kW) void ffn_few_kernel(FfnGemmArgs a) {
   }
 }
 
-template <int kMode, int kF, int kNB, int kW, int kD>
+template <bool kBF16, int kMode, int kF, int kNB, int kW, int kD>
 hipError_t launch_few(FfnGemmArgs a, hipStream_t stream) {
   const int grid = grid_with_copy(a.copy, a.n_feat / (16 * kF));
-  hipLaunchKernelGGL((ffn_few_kernel<kMode, kF, kNB, kW, kD>), dim3(grid, a.n_sets), dim3(64 * kW), 0, stream, a);
+  hipLaunchKernelGGL((ffn_few_kernel<kBF16, kMode, kF, kNB, kW, kD>), dim3(grid, a.n_sets, (a.cap + 16 * kNB - 1) / (16 * kNB)), dim3(64 * kW), 0, stream, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_ffn_few(const FfnGemmArgs& a, int mode, hipStream_t stream) {
+hipError_t launch_ffn_few(const FfnGemmArgs& a, int mode, bool bf16, hipStream_t stream) {
+  if (!bf16) return mode == 0 ? launch_few<false, 0, 1, 2, 4, 2>(a, stream) : launch_few<false, 1, 1, 1, 8, 3>(a, stream);
   if (mode == 0) {
-    if (a.cap <= 16) return launch_few<0, 1, 1, 4, 3>(a, stream);
-    if (a.cap <= 32) return launch_few<0, 2, 2, 4, 3>(a, stream);
-    return launch_few<0, 2, 4, 4, 2>(a, stream);
+    if (a.cap <= 16) return launch_few<true, 0, 1, 1, 4, 3>(a, stream);
+    if (a.cap <= 32) return launch_few<true, 0, 2, 2, 4, 3>(a, stream);
+    return launch_few<true, 0, 2, 4, 4, 2>(a, stream);
   }
-  if (a.cap <= 16) return launch_few<1, 1, 1, 8, 4>(a, stream);
-  if (a.cap <= 32) return launch_few<1, 1, 2, 8, 3>(a, stream);
-  return launch_few<1, 1, 4, 8, 2>(a, stream);
+  if (a.cap <= 16) return launch_few<true, 1, 1, 1, 8, 4>(a, stream);
+  if (a.cap <= 32) return launch_few<true, 1, 1, 2, 8, 3>(a, stream);
+  return launch_few<true, 1, 1, 4, 8, 2>(a, stream);
 }
 
 }  // namespace ce

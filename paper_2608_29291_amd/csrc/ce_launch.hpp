@@ -110,7 +110,7 @@ bool ffn_pruned_ok(const FfnGemmArgs& gateup, const FfnGemmArgs& down);
 // FFN GEMMs for at most kFewRows packed rows (bf16, see ce_ffn_few.hip); mode
 // 0 = gate/up, 1 = down. No split counters, no pruning.
 constexpr int kFewGapFeatures = 16;  // features per layer-gap slot of its down kernel
-hipError_t launch_ffn_few(const FfnGemmArgs& a, int mode, hipStream_t stream);
+hipError_t launch_ffn_few(const FfnGemmArgs& a, int mode, bool bf16, hipStream_t stream);
 
 // The same for mid-size packed counts (ce_ffn_mid.hip); down: a.part holds
 // pieces x cap x n_feat floats, one layer-gap slot per row.

@@ -31,6 +31,21 @@ def test_block(n, n_sets, d, F):
     print(f"[few n={n} sets={n_sets} d={d} F={F}] rel err {err:.2e}", flush=True)
 
 
+@pytest.mark.parametrize("n", [1, 16, 33, 200, 300])
+@pytest.mark.parametrize("n_sets", [1, 2])
+@pytest.mark.parametrize("d,F", [(64, 128), (320, 576)])  # 2, 4; 10, 18 lines of K, ragged over the waves
+def test_block_fp32(n, n_sets, d, F):
+    """fp32 on row tiles of this kernel; 1e-5 of max |Y| and of max |FFN|."""
+    import gpu_util as G
+    a = n // 3 if n_sets == 2 else 0
+    wl = make_workload("few32", [[(8, U), (max(n - a - 4, 0), K)], [(a, K | GN)]], d=d, F=F, r_c=32, r_e=32, keep=0.5,
+                       dtype="f32", seed=n, n_sets=n_sets, biases=True)
+    r = G.run_block(wl, inplace=bool(n & 1))
+    err, _ = G.check_block(wl, r)
+    print(f"[few fp32 n={n} sets={n_sets} d={d} F={F}] rel err {err:.2e}", flush=True)
+    np.testing.assert_array_equal(r["y"], G.run_block(wl)["y"])
+
+
 @pytest.mark.parametrize("n_sets", [1, 2])
 @pytest.mark.parametrize("n", [3, 40])
 def test_capacity_above_the_rows_and_determinism(n, n_sets):
