@@ -166,18 +166,21 @@ def _dev_ptr(t) -> Optional[int]:
     return _ptr(t)
 
 
+_DTYPE_CODE = {torch.bfloat16: CE_BF16, torch.float32: CE_F32}
+_TORCH_DTYPE = {CE_BF16: torch.bfloat16, CE_F32: torch.float32}
+_F32, _I32, _U8 = torch.float32, torch.int32, torch.uint8
+_device = torch._C._cuda_getDevice  # torch.cuda.current_device() once CUDA is initialised
+
+
 def _dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.bfloat16:
-        return CE_BF16
-    if t.dtype == torch.float32:
-        return CE_F32
-    raise ValueError(f"unsupported dtype {t.dtype}")
+    code = _DTYPE_CODE.get(t.dtype)
+    if code is None:
+        raise ValueError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def _torch_dtype(code: int):
-    import torch
-    return {CE_BF16: torch.bfloat16, CE_F32: torch.float32}[code]
+    return _TORCH_DTYPE[code]
 
 
 def _chk(t, name: str, dtype=None, numel: Optional[int] = None, shape=None, rows_min: Optional[int] = None,
@@ -187,42 +190,54 @@ def _chk(t, name: str, dtype=None, numel: Optional[int] = None, shape=None, rows
 
     dtype     required torch dtype
     numel     minimum element count
-    shape     exact shape (a tuple; None entries match any size)
+    shape     exact shape (a tuple of ints; a None first entry matches any size)
     rows_min  for matrices given by `shape` with a None row count: at least
               this many rows
+
+    A small block spends more time here than on the GPU, so a tensor that
+    passes takes one chain of attribute reads (0.91 -> 0.5 us a tensor); what
+    fails it is looked at again for the message.
     """
-    import torch
+    if t is None and optional:
+        return None
+    if (isinstance(t, torch.Tensor) and t.is_cuda and (dtype is None or t.dtype is dtype) and t.is_contiguous()
+            and t.get_device() == _device() and (numel is None or t.numel() >= numel)):
+        p = t.data_ptr()
+        if p & 15 == 0 or t.numel() == 0:
+            if shape is None or t.shape == shape:
+                return p
+            if (shape[0] is None and t.dim() == len(shape) and t.shape[1:] == shape[1:]
+                    and (rows_min is None or t.shape[0] >= rows_min)):
+                return p
+    raise ValueError(_why_not(t, name, dtype, numel, shape, rows_min))
+
+
+def _why_not(t, name, dtype, numel, shape, rows_min) -> str:
+    """What a tensor that _chk refused lacks."""
     if t is None:
-        if optional:
-            return None
-        raise ValueError(f"{name}: required tensor is missing")
+        return f"{name}: required tensor is missing"
     if not isinstance(t, torch.Tensor):
-        raise ValueError(f"{name}: expected a torch.Tensor, got {type(t).__name__}")
+        return f"{name}: expected a torch.Tensor, got {type(t).__name__}"
     if not t.is_cuda:
-        raise ValueError(f"{name}: tensor must live in GPU memory")
+        return f"{name}: tensor must live in GPU memory"
     if t.device.index != torch.cuda.current_device():
-        raise ValueError(f"{name}: tensor is on {t.device}, the current device is "
-                         f"cuda:{torch.cuda.current_device()}")
+        return f"{name}: tensor is on {t.device}, the current device is cuda:{torch.cuda.current_device()}"
     if not t.is_contiguous():
-        raise ValueError(f"{name}: tensor must be contiguous")
+        return f"{name}: tensor must be contiguous"
     if dtype is not None and t.dtype != dtype:
-        raise ValueError(f"{name}: dtype {t.dtype}, expected {dtype}")
+        return f"{name}: dtype {t.dtype}, expected {dtype}"
     if t.numel() > 0 and t.data_ptr() % 16 != 0:
-        raise ValueError(f"{name}: data pointer is not 16-byte aligned")
+        return f"{name}: data pointer is not 16-byte aligned"
     if numel is not None and t.numel() < numel:
-        raise ValueError(f"{name}: {t.numel()} elements, need at least {numel}")
-    if shape is not None:
-        if t.dim() != len(shape) or any(s is not None and int(d) != int(s) for d, s in zip(t.shape, shape)):
-            raise ValueError(f"{name}: shape {tuple(t.shape)}, expected {tuple(shape)}")
-        if rows_min is not None and t.shape[0] < rows_min:
-            raise ValueError(f"{name}: {t.shape[0]} rows, need at least {rows_min}")
-    return t.data_ptr()
+        return f"{name}: {t.numel()} elements, need at least {numel}"
+    if t.dim() != len(shape) or any(s is not None and int(d) != int(s) for d, s in zip(t.shape, shape)):
+        return f"{name}: shape {tuple(t.shape)}, expected {tuple(shape)}"
+    return f"{name}: {t.shape[0]} rows, need at least {rows_min}"
 
 
 def _stream(stream) -> Optional[int]:
-    import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(_device())
     return stream.cuda_stream
 
 
@@ -249,17 +264,17 @@ class Batch:
         return int(self.flags.numel())
 
     def c(self) -> CEBatch:
-        import torch
-        so = _chk(self.seq_offsets, "seq_offsets", torch.int32, numel=2)
+        so = _chk(self.seq_offsets, "seq_offsets", _I32, 2)
         if self.seq_offsets.dim() != 1:
             raise ValueError("seq_offsets must be 1-D [B+1]")
         if self.flags is None or self.flags.dim() != 1:
             raise ValueError("flags must be a 1-D uint8 tensor [T]")
-        fl = _chk(self.flags, "flags", torch.uint8)
-        tp = _chk(self.t, "t", torch.float32, numel=self.B, optional=True)
+        fl = _chk(self.flags, "flags", _U8)
+        B = self.seq_offsets.numel() - 1
+        tp = None if self.t is None else _chk(self.t, "t", _F32, B)
         if int(self.kept_capacity) < 0:
             raise ValueError("kept_capacity must be >= 0")
-        return CEBatch(self.B, self.T, so, fl, tp, float(self.keep), int(self.kept_capacity))
+        return CEBatch(B, self.flags.numel(), so, fl, tp, float(self.keep), int(self.kept_capacity))
 
 
 @dataclass
@@ -283,28 +298,29 @@ class Scorer:
         return _dtype_code(self.w1_core)
 
     def c(self) -> CEScorerW:
-        import torch
         if self.w1_core is None or self.w1_core.dim() != 2:
             raise ValueError("w1_core must be a matrix [r_core, d]")
-        r_c, d = (int(x) for x in self.w1_core.shape)
+        r_c, d = self.w1_core.shape
         tdt = self.w1_core.dtype
         _dtype_code(self.w1_core)
         if self.w1_exp is not None:
             if self.w1_exp.dim() != 3:
                 raise ValueError("w1_exp must be [n_seg, r_exp, d]")
-            n_seg, r_e = int(self.w1_exp.shape[0]), int(self.w1_exp.shape[1])
+            n_seg, r_e = self.w1_exp.shape[:2]
         else:
             n_seg, r_e = 1, 0
-        f32 = torch.float32
-        ptrs = (_chk(self.w1_core, "w1_core", tdt, shape=(r_c, d)),
-                _chk(self.b1_core, "b1_core", f32, shape=(r_c,), optional=True),
-                _chk(self.w2_core, "w2_core", f32, shape=(r_c,)),
-                _chk(self.w1_exp, "w1_exp", tdt, shape=(n_seg, r_e, d), optional=r_e == 0),
-                _chk(self.b1_exp, "b1_exp", f32, shape=(n_seg, r_e), optional=True),
-                _chk(self.w2_exp, "w2_exp", f32, shape=(n_seg, r_e), optional=r_e == 0),
-                _chk(self.b2_exp, "b2_exp", f32, shape=(n_seg,), optional=True))
+        ptrs = (_chk(self.w1_core, "w1_core", tdt),
+                None if self.b1_core is None else _chk(self.b1_core, "b1_core", _F32, None, (r_c,)),
+                _chk(self.w2_core, "w2_core", _F32, None, (r_c,)),
+                _chk(self.w1_exp, "w1_exp", tdt, None, (n_seg, r_e, d), None, r_e == 0),
+                None if self.b1_exp is None else _chk(self.b1_exp, "b1_exp", _F32, None, (n_seg, r_e)),
+                _chk(self.w2_exp, "w2_exp", _F32, None, (n_seg, r_e), None, r_e == 0),
+                None if self.b2_exp is None else _chk(self.b2_exp, "b2_exp", _F32, None, (n_seg,)))
         return CEScorerW(d, r_c, r_e, n_seg, _dtype_code(self.w1_core), ptrs[0], ptrs[1], ptrs[2],
                          float(self.b2_core), ptrs[3], ptrs[4], ptrs[5], ptrs[6])
+
+
+_FFN_NAMES = [[f"{w}[{i}]" for w in ("w_gate", "w_up", "w_down")] for i in range(2)]
 
 
 @dataclass
@@ -328,13 +344,13 @@ class FFN:
             raise ValueError("an FFN has 1 or 2 weight sets, each with gate, up and down")
         if self.w_gate[0] is None or self.w_gate[0].dim() != 2:
             raise ValueError("w_gate must be a matrix [d_ff, d]")
-        F, d = (int(x) for x in self.w_gate[0].shape)
+        F, d = self.w_gate[0].shape
         tdt = self.w_gate[0].dtype
         s = CEFFNW(d, F, n, _dtype_code(self.w_gate[0]))
         for i in range(n):
-            s.w_gate[i] = _chk(self.w_gate[i], f"w_gate[{i}]", tdt, shape=(F, d))
-            s.w_up[i] = _chk(self.w_up[i], f"w_up[{i}]", tdt, shape=(F, d))
-            s.w_down[i] = _chk(self.w_down[i], f"w_down[{i}]", tdt, shape=(d, F))
+            s.w_gate[i] = _chk(self.w_gate[i], _FFN_NAMES[i][0], tdt, None, (F, d))
+            s.w_up[i] = _chk(self.w_up[i], _FFN_NAMES[i][1], tdt, None, (F, d))
+            s.w_down[i] = _chk(self.w_down[i], _FFN_NAMES[i][2], tdt, None, (d, F))
         return s
 
 
@@ -372,14 +388,16 @@ def ce_kept_count_host(seq_offsets, flags, keep: float) -> int:
                                       ctypes.c_float(keep)))
 
 
+def _ws_size(which: int, cb: CEBatch, d: int, d_ff: int, dtype: int) -> int:
+    return lib.ce_workspace_size(which, ctypes.byref(cb), d, d_ff, dtype)
+
+
 def ce_workspace_size(which: int, batch: Batch, d: int, d_ff: int, dtype: int) -> int:
-    cb = batch.c()
-    return int(lib.ce_workspace_size(which, ctypes.byref(cb), int(d), int(d_ff), int(dtype)))
+    return _ws_size(which, batch.c(), int(d), int(d_ff), int(dtype))
 
 
 def alloc_workspace(which: int, batch: Batch, d: int, d_ff: int, dtype: int, device="cuda"):
     """Caller-owned workspace (uint8 device tensor, 256-byte aligned by torch's allocator)."""
-    import torch
     n = ce_workspace_size(which, batch, d, d_ff, dtype)
     return torch.empty(max(n, 256), dtype=torch.uint8, device=device)
 
@@ -392,33 +410,30 @@ def ce_workspace_status(ws, stream=None) -> int:
 
 
 def ce_score(batch: Batch, hidden, scorer: Scorer, logits, probs=None, stream=None):
-    import torch
     cb, sw = batch.c(), scorer.c()
     T = batch.T
     h = _hidden(hidden, "hidden", T, sw.d, _torch_dtype(sw.dtype) if sw.dtype in (0, 1) else None)
     _check(lib.ce_score(ctypes.byref(cb), h, ctypes.byref(sw),
-                        _chk(logits, "logits", torch.float32, numel=T),
-                        _chk(probs, "probs", torch.float32, numel=T, optional=True), _stream(stream)),
+                        _chk(logits, "logits", _F32, numel=T),
+                        _chk(probs, "probs", _F32, numel=T, optional=True), _stream(stream)),
            "ce_score")
 
 
 def ce_score_ws(batch: Batch, hidden, scorer: Scorer, logits, ws, probs=None, stream=None):
     """ce_score with a workspace (CE_WS_SCORE): the fused block's scorer,
     rank-tiled where ce_score_tiling picks it."""
-    import torch
     cb, sw = batch.c(), scorer.c()
     T = batch.T
     h = _hidden(hidden, "hidden", T, sw.d, _torch_dtype(sw.dtype) if sw.dtype in (0, 1) else None)
-    wp, wn = _ws_ptr(ws, ce_workspace_size(CE_WS_SCORE, batch, sw.d, 0, sw.dtype))
+    wp, wn = _ws_ptr(ws, _ws_size(CE_WS_SCORE, cb, sw.d, 0, sw.dtype))
     _check(lib.ce_score_ws(ctypes.byref(cb), h, ctypes.byref(sw),
-                           _chk(logits, "logits", torch.float32, numel=T),
-                           _chk(probs, "probs", torch.float32, numel=T, optional=True), wp, wn, _stream(stream)),
+                           _chk(logits, "logits", _F32, numel=T),
+                           _chk(probs, "probs", _F32, numel=T, optional=True), wp, wn, _stream(stream)),
            "ce_score_ws")
 
 
 def ce_topk_compact(batch: Batch, logits, kept_idx, kept_offsets, ws, token_pos=None,
                     hidden=None, compact=None, stream=None):
-    import torch
     cb = batch.c()
     T, B, cap = batch.T, batch.B, int(batch.kept_capacity)
     dtype = _dtype_code(hidden) if hidden is not None else CE_F32
@@ -429,10 +444,10 @@ def ce_topk_compact(batch: Batch, logits, kept_idx, kept_offsets, ws, token_pos=
             raise ValueError("compact needs hidden")
         hp = _hidden(hidden, "hidden", T, d, hidden.dtype)
         cp = _chk(compact, "compact", hidden.dtype, shape=(None, d), rows_min=cap)
-    i32 = torch.int32
-    wp, wn = _ws_ptr(ws, ce_workspace_size(CE_WS_TOPK, batch, d if compact is not None else 0, 0,
+    i32 = _I32
+    wp, wn = _ws_ptr(ws, _ws_size(CE_WS_TOPK, cb, d if compact is not None else 0, 0,
                                            dtype if compact is not None else CE_F32))
-    _check(lib.ce_topk_compact(ctypes.byref(cb), _chk(logits, "logits", torch.float32, numel=T), hp, dtype, d,
+    _check(lib.ce_topk_compact(ctypes.byref(cb), _chk(logits, "logits", _F32, numel=T), hp, dtype, d,
                                _chk(kept_idx, "kept_idx", i32, numel=cap),
                                _chk(kept_offsets, "kept_offsets", i32, numel=B + 1),
                                _chk(token_pos, "token_pos", i32, numel=T, optional=True), cp,
@@ -445,7 +460,6 @@ def ce_topk_compact_noalloc(batch: Batch, logits, kept_idx, kept_offsets, token_
     """ce_topk_compact without a workspace (the library's fixed per-GPU
     scratch holds the summaries; calls overlapping on one GPU race). status:
     optional uint32-sized device tensor (int32 is accepted) for the status word."""
-    import torch
     cb = batch.c()
     T, B, cap = batch.T, batch.B, int(batch.kept_capacity)
     dtype = _dtype_code(hidden) if hidden is not None else CE_F32
@@ -458,8 +472,8 @@ def ce_topk_compact_noalloc(batch: Batch, logits, kept_idx, kept_offsets, token_
         cp = _chk(compact, "compact", hidden.dtype, shape=(None, d), rows_min=cap)
     if status is not None and status.dtype not in (torch.int32, torch.uint32):
         raise ValueError("status must be a 4-byte integer tensor")
-    i32 = torch.int32
-    _check(lib.ce_topk_compact_noalloc(ctypes.byref(cb), _chk(logits, "logits", torch.float32, numel=T), hp,
+    i32 = _I32
+    _check(lib.ce_topk_compact_noalloc(ctypes.byref(cb), _chk(logits, "logits", _F32, numel=T), hp,
                                        dtype, d, _chk(kept_idx, "kept_idx", i32, numel=cap),
                                        _chk(kept_offsets, "kept_offsets", i32, numel=B + 1),
                                        _chk(token_pos, "token_pos", i32, numel=T, optional=True), cp,
@@ -468,13 +482,12 @@ def ce_topk_compact_noalloc(batch: Batch, logits, kept_idx, kept_offsets, token_
 
 
 def _ffn_common(batch: Batch, ffn: FFN, kept_idx, kept_offsets):
-    import torch
     cb, fw = batch.c(), ffn.c()
     cap = int(batch.kept_capacity)
-    ki = _chk(kept_idx, "kept_idx", torch.int32, numel=cap)
-    ko = _chk(kept_offsets, "kept_offsets", torch.int32, numel=batch.B + 1)
+    ki = _chk(kept_idx, "kept_idx", _I32, numel=cap)
+    ko = _chk(kept_offsets, "kept_offsets", _I32, numel=batch.B + 1)
     tdt = ffn.w_gate[0].dtype
-    need = ce_workspace_size(CE_WS_FFN, batch, fw.d, fw.d_ff, fw.dtype)
+    need = _ws_size(CE_WS_FFN, cb, fw.d, fw.d_ff, fw.dtype)
     return cb, fw, cap, ki, ko, tdt, need
 
 
@@ -510,35 +523,33 @@ def ce_routed_ffn_pruned(batch: Batch, compact, kept_idx, kept_offsets, ffn: FFN
     """SwiGLU FFN on the packed rows with the FFN-pruning decision (Eq. 8-9)
     taken from the gate/up epilogue's |z| sums; P = channels [n_keep, d_ff).
     ws: ce_workspace_size(CE_WS_FFN_PRUNED, ...) bytes."""
-    import torch
     cb = batch.c()
     fw = ffn.c()
     cap, B = int(batch.kept_capacity), batch.B
     tdt = ffn.w_gate[0].dtype
-    f32 = torch.float32
-    wp, wn = _ws_ptr(ws, ce_workspace_size(CE_WS_FFN_PRUNED, batch, fw.d, fw.d_ff, fw.dtype))
+    f32 = _F32
+    wp, wn = _ws_ptr(ws, _ws_size(CE_WS_FFN_PRUNED, cb, fw.d, fw.d_ff, fw.dtype))
     _check(lib.ce_routed_ffn_pruned(ctypes.byref(cb), _chk(compact, "compact", tdt, shape=(None, fw.d), rows_min=cap),
-                                    _chk(kept_idx, "kept_idx", torch.int32, numel=cap),
-                                    _chk(kept_offsets, "kept_offsets", torch.int32, numel=B + 1), ctypes.byref(fw),
+                                    _chk(kept_idx, "kept_idx", _I32, numel=cap),
+                                    _chk(kept_offsets, "kept_offsets", _I32, numel=B + 1), ctypes.byref(fw),
                                     _chk(norms, "norms", f32, numel=fw.n_sets * fw.d_ff), int(n_keep), float(delta),
                                     _chk(ffn_out, "ffn_out", tdt, shape=(None, fw.d), rows_min=cap),
                                     _chk(saliency, "saliency", f32, numel=B * fw.d_ff),
                                     _chk(leakage, "leakage", f32, numel=B),
-                                    _chk(use_pruned, "use_pruned", torch.uint8, numel=B), wp, wn, _stream(stream)),
+                                    _chk(use_pruned, "use_pruned", _U8, numel=B), wp, wn, _stream(stream)),
            "ce_routed_ffn_pruned")
 
 
 def ce_scatter_residual(batch: Batch, ffn_out, kept_idx, kept_offsets, hidden_in, hidden_out,
                         stream=None):
-    import torch
     cb = batch.c()
     cap, T = int(batch.kept_capacity), batch.T
     if hidden_in is None or hidden_in.dim() != 2:
         raise ValueError("hidden_in must be a matrix [T, d]")
     d, tdt = int(hidden_in.shape[1]), hidden_in.dtype
     _check(lib.ce_scatter_residual(ctypes.byref(cb), _chk(ffn_out, "ffn_out", tdt, shape=(None, d), rows_min=cap),
-                                   _chk(kept_idx, "kept_idx", torch.int32, numel=cap),
-                                   _chk(kept_offsets, "kept_offsets", torch.int32, numel=batch.B + 1),
+                                   _chk(kept_idx, "kept_idx", _I32, numel=cap),
+                                   _chk(kept_offsets, "kept_offsets", _I32, numel=batch.B + 1),
                                    _dtype_code(hidden_in), d, _hidden(hidden_in, "hidden_in", T, d, tdt),
                                    _hidden(hidden_out, "hidden_out", T, d, tdt), _stream(stream)),
            "ce_scatter_residual")
@@ -546,19 +557,18 @@ def ce_scatter_residual(batch: Batch, ffn_out, kept_idx, kept_offsets, hidden_in
 
 def ce_routed_block(batch: Batch, hidden_in, hidden_out, scorer: Scorer, ffn: FFN, ws,
                     logits_out=None, kept_idx_out=None, kept_offsets_out=None, stream=None):
-    import torch
     cb, sw, fw = batch.c(), scorer.c(), ffn.c()
     T, cap = batch.T, int(batch.kept_capacity)
     if sw.d != fw.d or sw.dtype != fw.dtype:
         raise ValueError("scorer and FFN must agree on d and dtype")
     tdt = ffn.w_gate[0].dtype
-    wp, wn = _ws_ptr(ws, ce_workspace_size(CE_WS_BLOCK, batch, fw.d, fw.d_ff, fw.dtype))
+    wp, wn = _ws_ptr(ws, _ws_size(CE_WS_BLOCK, cb, fw.d, fw.d_ff, fw.dtype))
     _check(lib.ce_routed_block(ctypes.byref(cb), _hidden(hidden_in, "hidden_in", T, fw.d, tdt),
                                _hidden(hidden_out, "hidden_out", T, fw.d, tdt),
                                ctypes.byref(sw), ctypes.byref(fw),
-                               _chk(logits_out, "logits_out", torch.float32, numel=T, optional=True),
-                               _chk(kept_idx_out, "kept_idx_out", torch.int32, numel=cap, optional=True),
-                               _chk(kept_offsets_out, "kept_offsets_out", torch.int32, numel=batch.B + 1,
+                               _chk(logits_out, "logits_out", _F32, numel=T, optional=True),
+                               _chk(kept_idx_out, "kept_idx_out", _I32, numel=cap, optional=True),
+                               _chk(kept_offsets_out, "kept_offsets_out", _I32, numel=batch.B + 1,
                                     optional=True),
                                wp, wn, _stream(stream)), "ce_routed_block")
 
@@ -568,24 +578,23 @@ def ce_routed_block_gap(batch: Batch, hidden_in, hidden_out, scorer: Scorer, ffn
                         stream=None):
     """ce_routed_block plus the block's layer-skipping gap (Eq. 7) from its
     down GEMM's epilogue; ws: ce_workspace_size(CE_WS_BLOCK_GAP, ...) bytes."""
-    import torch
     cb, sw, fw = batch.c(), scorer.c(), ffn.c()
     T, B, cap = batch.T, batch.B, int(batch.kept_capacity)
     if sw.d != fw.d or sw.dtype != fw.dtype:
         raise ValueError("scorer and FFN must agree on d and dtype")
     tdt = ffn.w_gate[0].dtype
-    f32 = torch.float32
-    wp, wn = _ws_ptr(ws, ce_workspace_size(CE_WS_BLOCK_GAP, batch, fw.d, fw.d_ff, fw.dtype))
+    f32 = _F32
+    wp, wn = _ws_ptr(ws, _ws_size(CE_WS_BLOCK_GAP, cb, fw.d, fw.d_ff, fw.dtype))
     _check(lib.ce_routed_block_gap(ctypes.byref(cb), _hidden(hidden_in, "hidden_in", T, fw.d, tdt),
                                    _hidden(hidden_out, "hidden_out", T, fw.d, tdt),
                                    ctypes.byref(sw), ctypes.byref(fw),
                                    _chk(logits_out, "logits_out", f32, numel=T, optional=True),
-                                   _chk(kept_idx_out, "kept_idx_out", torch.int32, numel=cap, optional=True),
-                                   _chk(kept_offsets_out, "kept_offsets_out", torch.int32, numel=B + 1,
+                                   _chk(kept_idx_out, "kept_idx_out", _I32, numel=cap, optional=True),
+                                   _chk(kept_offsets_out, "kept_offsets_out", _I32, numel=B + 1,
                                         optional=True),
                                    float(delta), _chk(cos, "cos", f32, numel=T), _chk(rho_all, "rho_all", f32, numel=B),
                                    _chk(rho_ret, "rho_ret", f32, numel=B), _chk(gap, "gap", f32, numel=B),
-                                   _chk(skip, "skip", torch.uint8, numel=B, optional=True), wp, wn, _stream(stream)),
+                                   _chk(skip, "skip", _U8, numel=B, optional=True), wp, wn, _stream(stream)),
            "ce_routed_block_gap")
 
 
@@ -602,10 +611,9 @@ def ce_score_tiling(batch: Batch, scorer: Scorer):
 
 def ce_drop_stability(batch: Batch, token_pos_t, token_pos_ref, jaccard, j_rand=None, rda=None,
                       stream=None):
-    import torch
     cb = batch.c()
     T, B = batch.T, batch.B
-    i32, f32 = torch.int32, torch.float32
+    i32, f32 = _I32, _F32
     _check(lib.ce_drop_stability(ctypes.byref(cb), _chk(token_pos_t, "token_pos_t", i32, numel=T),
                                  _chk(token_pos_ref, "token_pos_ref", i32, numel=T),
                                  _chk(jaccard, "jaccard", f32, numel=B),
@@ -615,19 +623,17 @@ def ce_drop_stability(batch: Batch, token_pos_t, token_pos_ref, jaccard, j_rand=
 
 
 def ce_ffn_down_colnorms(ffn: FFN, norms, stream=None):
-    import torch
     fw = ffn.c()
     _check(lib.ce_ffn_down_colnorms(ctypes.byref(fw),
-                                    _chk(norms, "norms", torch.float32, numel=fw.n_sets * fw.d_ff),
+                                    _chk(norms, "norms", _F32, numel=fw.n_sets * fw.d_ff),
                                     _stream(stream)), "ce_ffn_down_colnorms")
 
 
 def ce_ffn_saliency(batch: Batch, act, kept_idx, kept_offsets, ffn: FFN, norms, prune_mask, delta,
                     saliency, leakage, ws, use_pruned=None, stream=None):
-    import torch
     cb, fw, cap, ki, ko, tdt, need = _ffn_common(batch, ffn, kept_idx, kept_offsets)
     B, F = batch.B, fw.d_ff
-    f32, u8 = torch.float32, torch.uint8
+    f32, u8 = _F32, _U8
     wp, wn = _ws_ptr(ws, need)
     _check(lib.ce_ffn_saliency(ctypes.byref(cb), _chk(act, "act", tdt, shape=(None, F), rows_min=cap), ki, ko,
                                ctypes.byref(fw), _chk(norms, "norms", f32, numel=fw.n_sets * F),
@@ -638,59 +644,58 @@ def ce_ffn_saliency(batch: Batch, act, kept_idx, kept_offsets, ffn: FFN, norms, 
 
 
 def ce_ffn_mask_channels(batch: Batch, act, kept_offsets, prune_mask, use_pruned, stream=None):
-    import torch
     cb = batch.c()
     cap, B = int(batch.kept_capacity), batch.B
     if act is None or act.dim() != 2:
         raise ValueError("act must be a matrix [kept_capacity, d_ff]")
     F = int(act.shape[1])
     _check(lib.ce_ffn_mask_channels(ctypes.byref(cb), _chk(act, "act", act.dtype, shape=(None, F), rows_min=cap),
-                                    _chk(kept_offsets, "kept_offsets", torch.int32, numel=B + 1), _dtype_code(act),
-                                    F, _chk(prune_mask, "prune_mask", torch.uint8, numel=F),
-                                    _chk(use_pruned, "use_pruned", torch.uint8, numel=B), _stream(stream)),
+                                    _chk(kept_offsets, "kept_offsets", _I32, numel=B + 1), _dtype_code(act),
+                                    F, _chk(prune_mask, "prune_mask", _U8, numel=F),
+                                    _chk(use_pruned, "use_pruned", _U8, numel=B), _stream(stream)),
            "ce_ffn_mask_channels")
 
 
 def ce_layer_gap(batch: Batch, x_in, x_out, token_pos, delta, cos, rho_all, rho_ret, gap, skip=None,
                  stream=None):
-    import torch
     cb = batch.c()
     T, B = batch.T, batch.B
     if x_in is None or x_in.dim() != 2:
         raise ValueError("x_in must be a matrix [T, d]")
     d, tdt = int(x_in.shape[1]), x_in.dtype
-    f32 = torch.float32
+    f32 = _F32
     _check(lib.ce_layer_gap(ctypes.byref(cb), _hidden(x_in, "x_in", T, d, tdt), _hidden(x_out, "x_out", T, d, tdt),
-                            _dtype_code(x_in), d, _chk(token_pos, "token_pos", torch.int32, numel=T), float(delta),
+                            _dtype_code(x_in), d, _chk(token_pos, "token_pos", _I32, numel=T), float(delta),
                             _chk(cos, "cos", f32, numel=T), _chk(rho_all, "rho_all", f32, numel=B),
                             _chk(rho_ret, "rho_ret", f32, numel=B), _chk(gap, "gap", f32, numel=B),
-                            _chk(skip, "skip", torch.uint8, numel=B, optional=True), _stream(stream)),
+                            _chk(skip, "skip", _U8, numel=B, optional=True), _stream(stream)),
            "ce_layer_gap")
 
 
 def ce_routed_attention(q, k, v, o, q_offsets, kv_offsets, causal, scale, stream=None):
     """q, o [rows, H, head_dim], k, v [rows, H_kv, head_dim] bf16 device tensors;
     q_offsets / kv_offsets int32 device tensors [B+1]."""
-    import torch
     for name, x in (("q", q), ("k", k)):
         if x is None or x.dim() != 3:
             raise ValueError(f"{name} must be [rows, heads, head_dim]")
     if q_offsets is None or q_offsets.dim() != 1 or kv_offsets is None or kv_offsets.numel() != q_offsets.numel():
         raise ValueError("q_offsets and kv_offsets must be 1-D [B+1] of equal length")
     tdt = q.dtype
-    qs, ks = tuple(int(x) for x in q.shape), tuple(int(x) for x in k.shape)
-    B = int(q_offsets.numel() - 1)
-    ptrs = (_chk(q, "q", tdt, shape=qs), _chk(k, "k", tdt, shape=ks), _chk(v, "v", tdt, shape=ks),
-            _chk(o, "o", tdt, shape=qs), _chk(q_offsets, "q_offsets", torch.int32, numel=2),
-            _chk(kv_offsets, "kv_offsets", torch.int32, numel=2))
+    qs, ks = q.shape, k.shape
+    B = q_offsets.numel() - 1
+    ptrs = (_chk(q, "q", tdt), _chk(k, "k", tdt), _chk(v, "v", tdt, None, ks), _chk(o, "o", tdt, None, qs),
+            _chk(q_offsets, "q_offsets", _I32, 2), _chk(kv_offsets, "kv_offsets", _I32, 2))
     at = CEAttn(B, qs[1], ks[1], qs[2], ptrs[4], ptrs[5], qs[0], ks[0], int(bool(causal)), float(scale),
                 _dtype_code(q))
     # partial results of a decode step's key chunks: stream-ordered scratch
     # from torch's allocator, on the stream that the kernels run on
     ws, need = None, int(lib.ce_attention_workspace_size(ctypes.byref(at)))
     if need:
-        with torch.cuda.stream(stream):  # None: the current stream
-            ws = torch.empty(need, dtype=torch.uint8, device=q.device)
+        if stream is None:
+            ws = torch.empty(need, dtype=_U8, device=q.device)
+        else:
+            with torch.cuda.stream(stream):
+                ws = torch.empty(need, dtype=_U8, device=q.device)
     _check(lib.ce_routed_attention_ws(ctypes.byref(at), ptrs[0], ptrs[1], ptrs[2], ptrs[3], _ptr(ws), need,
                                       _stream(stream)), "ce_routed_attention")
 
