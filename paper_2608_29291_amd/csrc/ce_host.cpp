@@ -132,7 +132,9 @@ MidPlan mid_plan(int mode, int cap, int n_feat, int n_sets, int ns) {
     const int64_t items = (int64_t)((cap + 255) / 256 + n_sets - 1) * ((n_feat + 255) / 256);
     const GemmSplit sp = gemm_split(items, ns);
     const int full = sp.whole_x / kCusPerXcd;  // full rounds before the split ones
-    big = sp.pieces > 1 ? 38.0 + 1.3 * (full * ns + (double)ns / sp.pieces) + 0.25 * (double)items
+    // (two pieces: the last adds one other partial tile to its own sums)
+    big = sp.pieces > 1 ? (sp.pieces == 2 ? 20.0 : 38.0) + 1.3 * (full * ns + (double)ns / sp.pieces) +
+                              0.28 * (double)items
                         : 8.0 + 1.3 * ns * (double)((items + kCus - 1) / kCus);
   }
   best.use = best_c < 0.88 * big;  // clearly, the fit being what it is
