@@ -104,6 +104,9 @@ constexpr int kMidMaxPieces = 32;
 constexpr int kFewRows = 64;
 MidPlan mid_plan(int mode, int cap, int n_feat, int n_sets, int ns);
 
+// The one-workgroup-per-sequence signal kernels use wide workgroups up to this
+// many sequences (two of 1024 threads fit a CU).
+constexpr int kWideBatch = 512;
 // Sequences per batch: some grids put the sequence index in their y dimension.
 constexpr int kMaxBatch = 65535;
 // The FFN-saliency reduction splits each sequence's rows over at most this

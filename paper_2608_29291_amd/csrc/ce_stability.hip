@@ -14,12 +14,14 @@
 // sets is hypergeometric with mean E = a b / n; by Hoeffding's inequality for
 // sampling without replacement, P(|X - E| >= s) <= 2 exp(-2 s^2 / m) with
 // m = min(a, b), so the window E +- sqrt(48 m) misses less than 1e-41 of the
-// mass. Each thread takes a contiguous run of that window: the probability at
+// mass. Four threads take a contiguous run of that window: the probability at
 // the run's point nearest the mode comes from lgamma, the others from the
-// exact ratio of consecutive terms walking away from it (so the terms only
-// shrink and an underflow to zero is harmless). The per-thread sums are then
-// added in a fixed order.
+// exact ratio of consecutive terms walking away from it, one thread each way
+// (so the terms only shrink and an underflow to zero is harmless). The
+// per-thread sums are then added in a fixed order. Bound: latency, a few loads
+// in flight together and one lgamma.
 #include "ce_device.hpp"
+#include "ce_host.hpp"
 #include "ce_launch.hpp"
 #include "ce_router.h"
 
@@ -27,17 +29,19 @@ namespace ce {
 
 namespace {
 
-__device__ double log_choose(double n, double k) {
-  return lgamma(n + 1.0) - lgamma(k + 1.0) - lgamma(n - k + 1.0);
-}
-
 __device__ double jaccard_of(int64_t x, int64_t a, int64_t b) {
   const int64_t u = a + b - x;
   return u == 0 ? 1.0 : (double)x / (double)u;
 }
 
-// this thread's share of E[J] over the window (see above); every thread calls it
-__device__ double expected_random_jaccard_part(int64_t n, int64_t a, int64_t b, int tid) {
+// E[J] over the window (see above); every thread calls it, thread 0 gets the
+// sum. ln P(x) = ln C(a, x) + ln C(n - a, b - x) - ln C(n, b) takes nine
+// lgammas, five of them the same for every x: the four threads of a run take
+// one of its four each and eight spare threads the five, so the chain is one
+// lgamma long and not nine.
+template <int kThreads>
+__device__ double expected_random_jaccard(int64_t n, int64_t a, int64_t b, int tid, double* common, double* part) {
+  constexpr int kRuns = kThreads / 4 - 2;  // runs of the window: four threads each, two quads left
   int64_t xlo = a + b - n > 0 ? a + b - n : 0;
   int64_t xhi = a < b ? a : b;
   const double mean = (double)a * (double)b / (double)(n > 0 ? n : 1);
@@ -45,52 +49,87 @@ __device__ double expected_random_jaccard_part(int64_t n, int64_t a, int64_t b, 
   const int64_t wlo = (int64_t)floor(mean - half), whi = (int64_t)ceil(mean + half);
   xlo = wlo > xlo ? wlo : xlo;
   xhi = whi < xhi ? whi : xhi;
-  const int64_t per = (xhi - xlo + 256) / 256;
-  const int64_t c0 = xlo + (int64_t)tid * per;
+  const int run = tid >> 2, q4 = tid & 3;
+  const int64_t per = (xhi - xlo + kRuns) / kRuns;
+  const int64_t c0 = xlo + (int64_t)run * per;
   const int64_t c1 = c0 + per - 1 < xhi ? c0 + per - 1 : xhi;
-  if (c0 > c1) return 0.0;
-  int64_t xm = (int64_t)(((double)(a + 1) * (double)(b + 1)) / (double)(n + 2));
+  const bool mine = run < kRuns && c0 <= c1;
+  const int64_t xm = (int64_t)(((double)(a + 1) * (double)(b + 1)) / (double)(n + 2));
   const int64_t x0 = xm < c0 ? c0 : (xm > c1 ? c1 : xm);
-  const double p0 = exp(log_choose((double)a, (double)x0) + log_choose((double)(n - a), (double)(b - x0)) -
-                        log_choose((double)n, (double)b));
-  if (p0 == 0.0) return 0.0;
-  double sum = p0 * jaccard_of(x0, a, b);
-  const double c = (double)(n - a - b);
-  double q = p0;
-  for (int64_t x = x0; x < c1; ++x) {  // P(x + 1) / P(x) = (a - x)(b - x) / ((x + 1)(n - a - b + x + 1))
-    q *= ((double)(a - x) * (double)(b - x)) / ((double)(x + 1) * (c + (double)(x + 1)));
-    sum += q * jaccard_of(x + 1, a, b);
+  const int spare = tid - 4 * kRuns;
+  double arg = 1.0;
+  if (mine) arg = (double)(q4 == 0 ? x0 : q4 == 1 ? a - x0 : q4 == 2 ? b - x0 : n - a - b + x0) + 1.0;
+  else if (spare >= 0)
+    arg = (double)(spare == 0 ? a : spare == 1 ? n - a : spare == 2 ? n : spare == 3 ? b : n - b) + 1.0;
+  const double lg = lgamma(arg);
+  if (spare >= 0 && spare < 5) common[spare] = lg;
+  const int lane = threadIdx.x & 63, l0 = lane & ~3;
+  const double lx = __shfl(lg, l0), lax = __shfl(lg, l0 + 1), lbx = __shfl(lg, l0 + 2), lr = __shfl(lg, l0 + 3);
+  __syncthreads();
+  double sum = 0.0;
+  if (mine && q4 < 2) {
+    const double p0 = exp((common[0] - lx - lax) + (common[1] - lbx - lr) - (common[2] - common[3] - common[4]));
+    const double c = (double)(n - a - b);
+    double q = p0;
+    if (p0 == 0.0) {
+    } else if (q4 == 0) {
+      sum = p0 * jaccard_of(x0, a, b);
+      for (int64_t x = x0; x < c1; ++x) {  // P(x + 1) / P(x) = (a - x)(b - x) / ((x + 1)(n - a - b + x + 1))
+        q *= ((double)(a - x) * (double)(b - x)) / ((double)(x + 1) * (c + (double)(x + 1)));
+        sum += q * jaccard_of(x + 1, a, b);
+      }
+    } else {
+      for (int64_t x = x0; x > c0; --x) {  // P(x - 1) / P(x) = x (n - a - b + x) / ((a - x + 1)(b - x + 1))
+        q *= ((double)x * (c + (double)x)) / ((double)(a - x + 1) * (double)(b - x + 1));
+        sum += q * jaccard_of(x - 1, a, b);
+      }
+    }
   }
-  q = p0;
-  for (int64_t x = x0; x > c0; --x) {  // P(x - 1) / P(x) = x (n - a - b + x) / ((a - x + 1)(b - x + 1))
-    q *= ((double)x * (c + (double)x)) / ((double)(a - x + 1) * (double)(b - x + 1));
-    sum += q * jaccard_of(x - 1, a, b);
-  }
-  return sum;
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  if (lane == 0) part[tid >> 6] = sum;
+  __syncthreads();
+  double t = 0.0;
+  for (int w = 0; w < kThreads / 64; ++w) t += part[w];
+  return t;
 }
 
-__global__ __launch_bounds__(256) void stability_kernel(const int32_t* __restrict__ offs,
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void stability_kernel(const int32_t* __restrict__ offs,
                                                         const uint8_t* __restrict__ flags, int T,
                                                         const int32_t* __restrict__ tp_t,
                                                         const int32_t* __restrict__ tp_r,
                                                         float* __restrict__ jac,
                                                         float* __restrict__ jrand,
                                                         float* __restrict__ rda) {
-  __shared__ int cnt[4][4];
-  __shared__ double part[4];
+  constexpr int kWaves = kThreads / 64;
+  __shared__ int cnt[kWaves][4];
+  __shared__ double part[kWaves];
+  __shared__ double common[5];
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
   int o0 = offs[b], o1 = offs[b + 1];
   const int lo = o0 < 0 ? 0 : (o0 > T ? T : o0);
   const int hi = o1 < lo ? lo : (o1 > T ? T : o1);
   int n = 0, na = 0, nb = 0, nx = 0;
-  for (int i = lo + tid; i < hi; i += 256) {
-    if (flags[i] & CE_TOK_KEEP) continue;
-    const bool dt = tp_t[i] < 0, dr = tp_r[i] < 0;
-    n += 1;
-    na += dt;
-    nb += dr;
-    nx += dt && dr;
+  // four tokens per thread and step, their loads in flight together
+  for (int i0 = lo + tid; i0 < hi; i0 += 4 * kThreads) {
+    uint8_t f[4];
+    int32_t pt[4], pr[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = min(i0 + k * kThreads, hi - 1);
+      f[k] = flags[i];
+      pt[k] = tp_t[i];
+      pr[k] = tp_r[i];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const bool in = i0 + k * kThreads < hi && !(f[k] & CE_TOK_KEEP);
+      n += in;
+      na += in && pt[k] < 0;
+      nb += in && pr[k] < 0;
+      nx += in && pt[k] < 0 && pr[k] < 0;
+    }
   }
   for (int o = 32; o > 0; o >>= 1) {
     n += __shfl_xor(n, o);
@@ -106,7 +145,10 @@ __global__ __launch_bounds__(256) void stability_kernel(const int32_t* __restric
   }
   __syncthreads();
   int64_t c[4];
-  for (int k = 0; k < 4; ++k) c[k] = (int64_t)cnt[0][k] + cnt[1][k] + cnt[2][k] + cnt[3][k];
+  for (int k = 0; k < 4; ++k) {
+    c[k] = 0;
+    for (int w = 0; w < kWaves; ++w) c[k] += cnt[w][k];
+  }
   // c[0] = routable tokens, c[1] / c[2] = dropped at t / t_ref, c[3] = dropped at both
   double jr;
   const int64_t xlo = c[1] + c[2] - c[0] > 0 ? c[1] + c[2] - c[0] : 0;
@@ -114,11 +156,7 @@ __global__ __launch_bounds__(256) void stability_kernel(const int32_t* __restric
   if (xlo >= xhi) {
     jr = jaccard_of(xlo, c[1], c[2]);  // a single possible overlap
   } else {
-    double v = expected_random_jaccard_part(c[0], c[1], c[2], tid);
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if ((tid & 63) == 0) part[tid >> 6] = v;
-    __syncthreads();
-    jr = (part[0] + part[1]) + (part[2] + part[3]);
+    jr = expected_random_jaccard<kThreads>(c[0], c[1], c[2], tid, common, part);
   }
   if (tid != 0) return;
   const double j = jaccard_of(c[3], c[1], c[2]);
@@ -133,8 +171,15 @@ hipError_t launch_stability(const int32_t* seq_offsets, const uint8_t* flags, in
                             const int32_t* tp_t, const int32_t* tp_ref, float* jaccard, float* j_rand,
                             float* rda, hipStream_t stream) {
   if (B <= 0) return hipSuccess;
-  hipLaunchKernelGGL(stability_kernel, dim3(B), dim3(256), 0, stream, seq_offsets, flags, T, tp_t, tp_ref,
-                     jaccard, j_rand, rda);
+  // a few sequences leave the chip to themselves: 1024 threads each (4 x 4224
+  // tokens: 18.3 us with 256 threads and nine lgammas, 9.8 now); many fill it
+  // with 256
+  if (B <= kWideBatch)
+    hipLaunchKernelGGL(stability_kernel<1024>, dim3(B), dim3(1024), 0, stream, seq_offsets, flags, T, tp_t, tp_ref,
+                       jaccard, j_rand, rda);
+  else
+    hipLaunchKernelGGL(stability_kernel<256>, dim3(B), dim3(256), 0, stream, seq_offsets, flags, T, tp_t, tp_ref,
+                       jaccard, j_rand, rda);
   return hipGetLastError();
 }
 
