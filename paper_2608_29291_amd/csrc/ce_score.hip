@@ -36,27 +36,6 @@ namespace {
 constexpr int kSlabRow = 128;    // bytes of K per staged row
 constexpr int kMaxBlocks = 16;   // (r_core + r_exp) / 32 <= 512 / 32
 
-// s_waitcnt with a run-time vmcnt (0..63): the immediate is chosen by a switch.
-template <int N>
-__device__ __forceinline__ void wait_vm_upto(int n) {
-  if constexpr (N < 63) {
-    if (n > N) {
-      wait_vm_upto<N + 1>(n);
-      return;
-    }
-  }
-  wait_vmcnt<N>();
-}
-__device__ __forceinline__ void wait_vm(int n) {
-  n = n < 0 ? 0 : (n > 63 ? 63 : n);
-  // split first so the chain of compares stays short
-  if (n < 16) wait_vm_upto<0>(n);
-  else if (n < 32) wait_vm_upto<16>(n);
-  else if (n < 48) wait_vm_upto<32>(n);
-  else wait_vm_upto<48>(n);
-}
-
-
 // Exclusive prefix sum over the 256 threads of a workgroup (4 waves), plus
 // the total; scr: 4 ints of LDS. Every thread must call it.
 __device__ __forceinline__ int block_excl_scan(int v, int* scr, int& total) {
@@ -341,15 +320,6 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
   }
   const int nbc = a.r_core / 32;
   const int nb = nbc + (any_gen ? a.r_exp / 32 : 0);  // weight blocks of this tile (<= 16)
-  const int stage = (kTM + 32 * nb) * kSlabRow;
-  // two slabs in flight: deeper rings measured slower (the extra LDS DMA in
-  // flight only adds queueing); a stage is at most (32 + 512) x 128 B = 68 KB
-  // for 32-token tiles and (128 + 384) x 128 B = 64 KB for 128-token tiles
-  // (the launcher takes those only for r_core + r_exp <= 384)
-  int nstage = kLds / stage;
-  nstage = nstage > 3 ? 3 : nstage;
-  const int per_slab = MB + nb;      // DMA instructions per wave per slab
-
   // ---- DMA plan: instruction i of a slab covers stage rows 8i .. 8i + 7 and
   //      belongs to wave i % 4: wave w fetches token rows 8w .. 8w + 7 and rows
   //      8w .. 8w + 7 of every weight block ----
@@ -384,32 +354,18 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
   // summary workgroups in front.
   const int nk_all = a.k_bytes / kSlabRow;
   const int rot = (int)((unsigned)tile % (unsigned)nk_all);
-  auto dma = [&](int kb, int buf) __attribute__((always_inline)) {
-    lds_char* st = ring + buf * stage;
-    int ks = kb + rot;
-    ks = ks >= nk_all ? ks - nk_all : ks;
-    const int soff = ks * kSlabRow;
-#pragma unroll
-    for (int j = 0; j < MB; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(trs, st + (32 * j + 8 * wave) * kSlabRow, 16, (int)t_voff[j], soff, 0,
-                                               0);
-    // one loop per weight matrix: each instruction's resource is fixed
-    for (int blk = 0; blk < nbc; ++blk)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(crs, st + (kTM + 32 * blk + 8 * wave) * kSlabRow, 16,
-                                               (int)w_voff, soff + (int)(32 * blk * a.h_ld), 0, 0);
-    for (int blk = nbc; blk < nb; ++blk)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ers, st + (kTM + 32 * blk + 8 * wave) * kSlabRow, 16,
-                                               (int)w_voff, soff + (int)(32 * (blk - nbc) * a.h_ld), 0, 0);
-  };
-
   // ---- main loop: wave w accumulates its blocks w, w + 4, w + 8, w + 12;
-  //      the block count is a compile-time constant of each variant, so a
-  //      slab's fragments are all read before its MFMAs are issued ----
+  //      the tile's block count is a compile-time constant of each variant, so
+  //      a slab's fragments are all read before its MFMAs are issued, its DMAs
+  //      are unrolled and the waits for them are immediates (chosen at run time
+  //      they took a tree of branches in every slab). What bounds a call of up to
+  //      8192 tokens is this chain of slabs, the same for 16 tokens: d 1536, 128
+  //      ranks 16.7 -> 12.3 us, with 64 more for generation 20.1 -> 16.1; d 3584,
+  //      256 ranks 44 -> 32, with 128 more 46.8 -> 44.5; fp32 d 256 11.0 -> 10.0 ----
   const int lrow = lane & 31;
   const int lhalf = lane >> 5;
   const uint32_t rkey = (uint32_t)((lrow >> 1) & 7);
   const int nk = a.k_bytes / kSlabRow;
-  const int nbw = (nb - wave + 3) / 4;  // blocks of this wave (0..4)
   // the epilogue's b1 / w2 values (lane l < 32: b1 of rank l of the block,
   // l >= 32: w2 of rank l - 32), loaded now and parked in LDS after the loop
   float epv[kMaxBlocks / 4];
@@ -425,13 +381,47 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
       epv[i] = lhalf ? w2[r] : (b1 ? b1[r] : 0.0f);
     }
   }
-  const int pre = min(nk, nstage - 1);
-  for (int s = 0; s < pre; ++s) dma(s, s);
   float pc[MB], pe[MB];
 #pragma unroll
   for (int j = 0; j < MB; ++j) pc[j] = pe[j] = 0.0f;
-  auto run = [&](auto nbw_c) __attribute__((always_inline)) {
-    constexpr int NBW = decltype(nbw_c)::value;
+  auto run = [&](auto nb_c) __attribute__((always_inline)) {
+    constexpr int NB = decltype(nb_c)::value;     // weight blocks of the tile
+    constexpr int NBW = (NB + 3) / 4;             // of a wave, at most
+    auto has = [&](int i) __attribute__((always_inline)) {  // does this wave own a block i?
+      return 4 * i + 3 < NB || wave + 4 * i < NB;
+    };
+    // a wave without a last block repeats another's and leaves the sums out: no
+    // branch between a slab's reads and its MFMAs
+    int row_blk[NBW];
+#pragma unroll
+    for (int i = 0; i < NBW; ++i) row_blk[i] = has(i) ? wave + 4 * i : 0;
+    constexpr int kStage = (kTM + 32 * NB) * kSlabRow;
+    constexpr int kPer = MB + NB;  // DMA instructions per wave and slab
+    // two slabs in flight: six measured the same from 16 to 8192 tokens. A stage
+    // is at most (32 + 512) x 128 B = 68 KB for 32-token tiles and (128 + 384)
+    // x 128 B = 64 KB for 128-token tiles (the launcher takes those only for
+    // r_core + r_exp <= 384)
+    constexpr int kRing = kLds / kStage < 3 ? kLds / kStage : 3;
+    static_assert(kRing >= 2, "a slab is multiplied while the next arrives");
+    auto dma = [&](int kb, int buf) __attribute__((always_inline)) {
+      lds_char* st = ring + buf * kStage;
+      int ks = kb + rot;
+      ks = ks >= nk_all ? ks - nk_all : ks;
+      const int soff = ks * kSlabRow;
+#pragma unroll
+      for (int j = 0; j < MB; ++j)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(trs, st + (32 * j + 8 * wave) * kSlabRow, 16, (int)t_voff[j], soff,
+                                                 0, 0);
+#pragma unroll
+      for (int blk = 0; blk < NB; ++blk) {
+        lds_char* dst = st + (kTM + 32 * blk + 8 * wave) * kSlabRow;
+        const bool core = blk < nbc;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(core ? crs : ers, dst, 16, (int)w_voff,
+                                                 soff + (int)(32 * (core ? blk : blk - nbc) * a.h_ld), 0, 0);
+      }
+    };
+    const int pre = min(nk, kRing - 1);
+    for (int s = 0; s < pre; ++s) dma(s, s);
     // a 32-token tile keeps two accumulators per block (even and odd K steps),
     // halving the chain of dependent MFMAs; they are added before the epilogue
     constexpr int NACC = MB == 1 ? 2 : 1;
@@ -444,12 +434,15 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
         for (int e = 0; e < NACC; ++e) acc[i][j][e] = f32x16_t{};
     int buf = 0;
     for (int kb = 0; kb < nk; ++kb) {
-      // slab kb must have landed; the later slabs already issued may stay in flight
-      const int ahead = min(nk - 1 - kb, nstage - 2);
-      wait_vm(ahead * per_slab);
+      // slab kb must have landed; the later slabs already issued may stay in
+      // flight (the last few are waited for together)
+      if (kb + kRing - 2 < nk)
+        wait_vmcnt<(kRing - 2) * kPer>();
+      else
+        wait_vmcnt<0>();
       lds_barrier();
-      if constexpr (NBW > 0) {
-        const char* st = smem + buf * stage;
+      {
+        const char* st = smem + buf * kStage;
         u32x4_t fb[4][MB], fa[4][NBW];
 #pragma unroll
         for (int step = 0; step < 4; ++step) {
@@ -459,8 +452,7 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
             fb[step][j] = *reinterpret_cast<const u32x4_t*>(st + (32 * j + lrow) * kSlabRow + off);
 #pragma unroll
           for (int i = 0; i < NBW; ++i)
-            fa[step][i] = *reinterpret_cast<const u32x4_t*>(
-                st + (kTM + 32 * (wave + 4 * i) + lrow) * kSlabRow + off);
+            fa[step][i] = *reinterpret_cast<const u32x4_t*>(st + (kTM + 32 * row_blk[i] + lrow) * kSlabRow + off);
         }
 #pragma unroll
         for (int step = 0; step < 4; ++step)
@@ -470,14 +462,14 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
             for (int j = 0; j < MB; ++j) mfma_step<kBF16>(acc[i][j][NACC == 2 ? (step & 1) : 0], fa[step][i], fb[step][j]);
       }
       // every wave is past slab kb - 1 (the barrier above): its buffer receives
-      // slab kb + nstage - 1. Issued after this slab's fragment reads, so no
+      // slab kb + kRing - 1. Issued after this slab's fragment reads, so no
       // LDS read follows a DMA without a barrier in between.
-      if (kb + nstage - 1 < nk) {
-        int nbuf = buf + nstage - 1;
-        nbuf = nbuf >= nstage ? nbuf - nstage : nbuf;
-        dma(kb + nstage - 1, nbuf);
+      if (kb + kRing - 1 < nk) {
+        int nbuf = buf + kRing - 1;
+        nbuf = nbuf >= kRing ? nbuf - kRing : nbuf;
+        dma(kb + kRing - 1, nbuf);
       }
-      buf = buf + 1 == nstage ? 0 : buf + 1;
+      buf = buf + 1 == kRing ? 0 : buf + 1;
     }
     // ---- epilogue: b1, SiLU, w2 over this wave's blocks; core and expansion kept apart ----
 #pragma unroll
@@ -485,6 +477,7 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
 #pragma unroll
     for (int i = 0; i < NBW; ++i) {
       const int blk = wave + 4 * i;
+      if (!has(i)) continue;
       const bool hb = (blk >= nbc ? a.b1e : a.b1c) != nullptr;
 #pragma unroll
       for (int j = 0; j < MB; ++j) {
@@ -502,14 +495,30 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
       }
     }
   };
-  switch (nbw) {
-    case 0: run(std::integral_constant<int, 0>{}); break;
+  switch (nb) {
     case 1: run(std::integral_constant<int, 1>{}); break;
     case 2: run(std::integral_constant<int, 2>{}); break;
     case 3: run(std::integral_constant<int, 3>{}); break;
+    case 4: run(std::integral_constant<int, 4>{}); break;
+    case 5: run(std::integral_constant<int, 5>{}); break;
+    case 6: run(std::integral_constant<int, 6>{}); break;
+    case 7: run(std::integral_constant<int, 7>{}); break;
+    case 8: run(std::integral_constant<int, 8>{}); break;
+    case 9: run(std::integral_constant<int, 9>{}); break;
+    case 10: run(std::integral_constant<int, 10>{}); break;
+    case 11: run(std::integral_constant<int, 11>{}); break;
+    case 12: run(std::integral_constant<int, 12>{}); break;
     default:
       // 128-token tiles are launched for at most 12 rank blocks (3 per wave)
-      if constexpr (kTM == 32) run(std::integral_constant<int, 4>{});
+      if constexpr (kTM == 32) {
+        switch (nb) {
+          case 13: run(std::integral_constant<int, 13>{}); break;
+          case 14: run(std::integral_constant<int, 14>{}); break;
+          case 15: run(std::integral_constant<int, 15>{}); break;
+          case 16: run(std::integral_constant<int, 16>{}); break;
+          default: break;
+        }
+      }
       break;
   }
 #pragma unroll
