@@ -351,18 +351,20 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(DecodeArgs a) {
       float m_new = m;
 #pragma unroll
       for (int i = 0; i < 8; ++i) m_new = fmaxf(m_new, mc[i]);
-      if (m_new == -__builtin_inff()) continue;  // no key seen yet
-      const float al = __builtin_amdgcn_exp2f((m - m_new) * a.scale_log2);
+      // (a maximum of -inf is a chunk whose keys are hidden or whose scores are
+      // all NaN: its output, 0 or NaN, counts with weight 0, as a wave's does in
+      // the launch before; loads repeated past the last chunk don't count)
+      const float al = m_new == -__builtin_inff() ? 1.0f : __builtin_amdgcn_exp2f((m - m_new) * a.scale_log2);
       l *= al;
       x0 *= al;
       x1 *= al;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const float w = c0 + i < n && mc[i] != -__builtin_inff()
-                            ? __builtin_amdgcn_exp2f((mc[i] - m_new) * a.scale_log2) : 0.0f;
-        l = fmaf(lc[i], w, l);
-        x0 = fmaf(y0[i], w, x0);
-        x1 = fmaf(y1[i], w, x1);
+        const bool in = c0 + i < n;
+        const float w = in && mc[i] != -__builtin_inff() ? __builtin_amdgcn_exp2f((mc[i] - m_new) * a.scale_log2) : 0.0f;
+        l = fmaf(in ? lc[i] : 0.0f, w, l);
+        x0 = fmaf(in ? y0[i] : 0.0f, w, x0);
+        x1 = fmaf(in ? y1[i] : 0.0f, w, x1);
       }
       m = m_new;
     }

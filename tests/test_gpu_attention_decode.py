@@ -65,6 +65,46 @@ def test_few_queries(name, causal):
         np.testing.assert_array_equal(got, run(q, k, v, qo, ko, causal, ws))
 
 
+@pytest.mark.parametrize("kind", ["query", "key prefix", "one key", "score", "value", "infinite value"])
+@pytest.mark.parametrize("causal", [False, True])
+def test_not_finite(kind, causal):
+    """NaN and infinity come out of the rows and heads that see them, and of no
+    others, whether a cache is cut into chunks (of 128 keys here) or not."""
+    h, hkv = 4, 2
+    q, k, v, qo, ko = make_attention_inputs([1, 1], [1805, 300], h, hkv, DH, seed=5)
+    if kind == "query":
+        q[0, 1, 7] = q[1, 0, 3] = np.nan
+        want = [((0, 1), np.nan), ((1, 0), np.nan)]
+    elif kind == "key prefix":  # the first ten chunks of one cache, all of the other
+        k[:1400] = k[1805:] = np.nan
+        want = [(..., np.nan)]
+    elif kind == "one key":
+        k[1700, 0, 5] = np.nan
+        want = [((0, slice(0, 2)), np.nan)]
+    elif kind == "score":  # 1e40: infinite in fp32, inf - inf
+        q[0, 2, 5] = k[900, 1, 5] = 1e20
+        q[0, 3, 5] = 0
+        want = [((0, 2), np.nan)]
+    elif kind == "value":
+        v[1100, 0, 64] = np.nan
+        want = [((0, slice(0, 2), 64), np.nan)]
+    else:  # in the last chunk, the fifteenth
+        v[1800, 1, 9] = np.inf
+        want = [((0, slice(2, 4), 9), np.inf)]
+    with np.errstate(all="ignore"):
+        ref = oa.attention(q, k, np.where(np.isfinite(v), v, 0), qo, ko, hkv, causal, DH ** -0.5)
+    for at, x in want:
+        ref[at] = x
+    tol = 2.0 ** -8 * float(np.max(np.abs(v[np.isfinite(v)]))) + 1e-6
+    for ws in (True, False):
+        got = run(q, k, v, qo, ko, causal, ws)
+        print(f"[decode {kind} causal={causal} ws={ws}] {np.isnan(got).sum()} NaN, {np.isinf(got).sum()} inf", flush=True)
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+        np.testing.assert_array_equal(np.isinf(got), np.isinf(ref))
+        fin = np.isfinite(ref)
+        assert np.max(np.abs(got[fin] - ref[fin]), initial=0) <= tol
+
+
 def test_own_stream_and_capture():
     """On another stream, and captured with replays between eager calls."""
     import torch
