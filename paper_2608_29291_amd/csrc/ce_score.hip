@@ -336,10 +336,11 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
   }
   const uint32_t w_voff = (uint32_t)(trow * a.h_ld) + chunk_off;
   const __amdgpu_buffer_rsrc_t trs = make_rsrc(a.hidden + (int64_t)lo * a.h_ld, (uint32_t)(n * a.h_ld));
-  const __amdgpu_buffer_rsrc_t crs = make_rsrc(a.w1c, (uint32_t)(a.r_core * a.h_ld));
-  const __amdgpu_buffer_rsrc_t ers =
-      make_rsrc(any_gen ? a.w1e + (int64_t)m * a.r_exp * a.h_ld : a.w1c,
-                (uint32_t)((any_gen ? a.r_exp : a.r_core) * a.h_ld));
+  // rows of the tile's weights, core then expansion, at 32 blk h_ld behind the
+  // base that block blk takes: both bases cover all of them
+  const uint32_t w_bytes = (uint32_t)((a.r_core + a.r_exp) * a.h_ld);
+  const char* const w_core = a.w1c;
+  const char* const w_exp = any_gen ? a.w1e + ((int64_t)m * a.r_exp - a.r_core) * a.h_ld : a.w1c;
   // The ring base passes through an empty asm: the compiler then cannot tie the
   // DMA writes to the fragment reads and leaves their ordering to the explicit
   // vmcnt waits and barriers of the loop, instead of draining every load in
@@ -361,7 +362,10 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
   //      they took a tree of branches in every slab). What bounds a call of up to
   //      8192 tokens is this chain of slabs, the same for 16 tokens: d 1536, 128
   //      ranks 16.7 -> 12.3 us, with 64 more for generation 20.1 -> 16.1; d 3584,
-  //      256 ranks 44 -> 32, with 128 more 46.8 -> 44.5; fp32 d 256 11.0 -> 10.0 ----
+  //      256 ranks 44 -> 32, with 128 more 46.8 -> 45; fp32 d 256 11.0 -> 10.0.
+  //      128-token tiles, 11264 tokens at d 3584: 256 ranks 76 -> 62, with 128 more
+  //      106 and 107 (112 while the variants' loops kept values in each other's
+  //      registers and in scratch memory; no kernel here spills any more) ----
   const int lrow = lane & 31;
   const int lhalf = lane >> 5;
   const uint32_t rkey = (uint32_t)((lrow >> 1) & 7);
@@ -412,12 +416,17 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
       for (int j = 0; j < MB; ++j)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(trs, st + (32 * j + 8 * wave) * kSlabRow, 16, (int)t_voff[j], soff,
                                                  0, 0);
+      // (the block where the expansion starts through an empty asm: hoisted out
+      // of the K loop, the blocks' bases and offsets spilled 138 SGPRs)
+      int nc = nbc;
+      asm volatile("" : "+s"(nc));
+      int woff = soff;
 #pragma unroll
       for (int blk = 0; blk < NB; ++blk) {
-        lds_char* dst = st + (kTM + 32 * blk + 8 * wave) * kSlabRow;
-        const bool core = blk < nbc;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(core ? crs : ers, dst, 16, (int)w_voff,
-                                                 soff + (int)(32 * (core ? blk : blk - nbc) * a.h_ld), 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(blk < nc ? w_core : w_exp, w_bytes),
+                                                 st + (kTM + 32 * blk + 8 * wave) * kSlabRow, 16, (int)w_voff, woff, 0,
+                                                 0);
+        woff += 32 * (int)a.h_ld;
       }
     };
     const int pre = min(nk, kRing - 1);
@@ -433,6 +442,9 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
 #pragma unroll
         for (int e = 0; e < NACC; ++e) acc[i][j][e] = f32x16_t{};
     int buf = 0;
+    // (at least one slab: with three blocks of 128 tokens, copying the sums around
+    // a loop that could be skipped takes the registers that are left and spills)
+    if constexpr (MB * NBW == 12) __builtin_assume(nk > 0);
     for (int kb = 0; kb < nk; ++kb) {
       // slab kb must have landed; the later slabs already issued may stay in
       // flight (the last few are waited for together)

@@ -1,6 +1,7 @@
 """The single-launch scorer at every number of 32-rank blocks it has a variant
-for (1 to 16 with 32-token tiles, core and expansion split in several ways),
-fp32 and bf16, K of one to ten slabs, against float64.
+for (1 to 16 with 32-token tiles, 1 to 12 with 128-token tiles, core and
+expansion split in several ways), fp32 and bf16, K of one to ten slabs, against
+float64.
 
 Bar: fp32 products of bf16 or fp32 inputs, summed in fp32 over d <= 320 values
 and 512 ranks: each logit is off by at most about sqrt(d + r) 2^-24 of the sum
@@ -24,10 +25,8 @@ def reference(torch, h, flags, m, sc, ce):
     return out
 
 
-@pytest.mark.parametrize("slabs", [1, 2, 3, 5])
-@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-@pytest.mark.parametrize("core,exp", [(1, 1), (2, 1), (3, 2), (4, 4), (6, 1), (8, 3), (9, 1), (9, 4), (12, 2), (15, 1)])
-def test_rank_blocks(core, exp, dtype, slabs):
+def check(T, und, core, exp, dtype, slabs):
+    """T tokens, `und` for understanding, then generation with four kept ones."""
     import torch
 
     import paper_2608_29291_amd as ce
@@ -41,10 +40,9 @@ def test_rank_blocks(core, exp, dtype, slabs):
     r_c, r_e = 32 * core, 32 * exp
     sc = ce.Scorer(rnd(r_c, d, to=dt), rnd(r_c), rnd(4, r_e, d, to=dt), rnd(4, r_e), b1_core=rnd(r_c), b2_core=0.25,
                    b1_exp=rnd(4, r_e), b2_exp=rnd(4))
-    T = 77  # an understanding tile (core blocks only), a mixed one, a ragged one
     flags = torch.zeros(T, dtype=torch.uint8)
-    flags[40:] = ce.CE_TOK_GEN
-    flags[50:54] = ce.CE_TOK_KEEP
+    flags[und:] = ce.CE_TOK_GEN
+    flags[und + 10:und + 14] = ce.CE_TOK_KEEP
     flags = flags.cuda()
     h = torch.randn((T, d), generator=g, device="cuda").to(dt)
     batch = ce.Batch(torch.tensor([0, T], dtype=torch.int32).cuda(), flags, torch.tensor([0.6]).cuda(), 0.5, T)
@@ -55,5 +53,22 @@ def test_rank_blocks(core, exp, dtype, slabs):
     fin = torch.isfinite(ref)
     assert torch.equal(torch.isfinite(logits), fin)
     err = ((logits.double() - ref)[fin].abs().max() / ref[fin].abs().max()).item()
-    print(f"[score blocks {core}+{exp} {dtype} slabs={slabs}] err {err:.1e}", flush=True)
+    print(f"[score blocks T={T} {core}+{exp} {dtype} slabs={slabs}] err {err:.1e}", flush=True)
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("slabs", [1, 2, 3, 5])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("core,exp", [(1, 1), (2, 1), (3, 2), (4, 4), (6, 1), (8, 3), (9, 1), (9, 4), (12, 2), (15, 1)])
+def test_rank_blocks(core, exp, dtype, slabs):
+    check(77, 40, core, exp, dtype, slabs)  # an understanding tile (core blocks only), a mixed one, a ragged one
+
+
+@pytest.mark.parametrize("slabs", [1, 2, 3, 5])
+@pytest.mark.parametrize("core,exp", [(n, 1) for n in range(1, 12)] + [(4, 8), (8, 4)])
+def test_rank_blocks_of_large_tiles(core, exp, slabs):
+    """128-token tiles: `core` blocks up to the mixed tile, core + exp after it."""
+    T = 16500  # 516 tiles of 32 tokens are three rounds of the 256 CUs, 129 of 128 are one: always the larger
+    rounds = [-(-T // t // 256) * (t + 32 * (core + exp)) for t in (32, 128)]
+    assert rounds[1] < rounds[0]
+    check(T, 6000, core, exp, "bf16", slabs)
