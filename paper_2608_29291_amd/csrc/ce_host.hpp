@@ -104,9 +104,12 @@ constexpr int kMidMaxPieces = 32;
 constexpr int kFewRows = 64;
 MidPlan mid_plan(int mode, int cap, int n_feat, int n_sets, int ns);
 
-// The one-workgroup-per-sequence signal kernels use wide workgroups up to this
-// many sequences (two of 1024 threads fit a CU).
-constexpr int kWideBatch = 512;
+// The one-workgroup-per-sequence signal kernels use workgroups of 1024 threads
+// when the sequences (at most one per CU) hold this many tokens on average; the
+// kernels state where their lines lie.
+constexpr bool wide_signal(int B, int T, int tokens) {
+  return B <= kXcdCount * kCusPerXcd && (int64_t)B * tokens <= T;
+}
 // Sequences per batch: some grids put the sequence index in their y dimension.
 constexpr int kMaxBatch = 65535;
 // The FFN-saliency reduction splits each sequence's rows over at most this

@@ -17,6 +17,7 @@
 // the token's cosine; then a workgroup per sequence adds the cosines in fp64
 // in a fixed order. Results are deterministic.
 #include "ce_device.hpp"
+#include "ce_host.hpp"
 #include "ce_launch.hpp"
 
 namespace ce {
@@ -110,8 +111,9 @@ __global__ __launch_bounds__(256) void token_cos_parts_kernel(const double* __re
   }
 }
 
-// A workgroup per sequence. Bound: latency, so many loads are in flight.
-template <int kGapThreads>
+// A workgroup per sequence, kPer tokens per thread and step with their loads in
+// flight together. Bound: latency.
+template <int kGapThreads, int kPer>
 __global__ __launch_bounds__(kGapThreads) void gap_kernel(const int32_t* __restrict__ offs, int T,
                                                   const int32_t* __restrict__ token_pos,
                                                   const float* __restrict__ cos_tok, float delta,
@@ -127,18 +129,17 @@ __global__ __launch_bounds__(kGapThreads) void gap_kernel(const int32_t* __restr
   const int hi = o1 < lo ? lo : (o1 > T ? T : o1);
   double sa = 0.0, sr = 0.0;
   int nr = 0;
-  // four tokens per thread and step, their loads in flight together
-  for (int i0 = lo + tid; i0 < hi; i0 += 4 * kGapThreads) {
-    float x[4];
-    int32_t p[4];
+  for (int i0 = lo + tid; i0 < hi; i0 += kPer * kGapThreads) {
+    float x[kPer];
+    int32_t p[kPer];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int i = min(i0 + k * kGapThreads, hi - 1);
+    for (int k = 0; k < kPer; ++k) {
+      const int i = kPer == 1 ? i0 : min(i0 + k * kGapThreads, hi - 1);
       x[k] = cos_tok[i];
       p[k] = token_pos[i];
     }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < kPer; ++k) {
       if (i0 + k * kGapThreads >= hi) break;
       const double c = x[k];
       sa += c;
@@ -177,15 +178,20 @@ __global__ __launch_bounds__(kGapThreads) void gap_kernel(const int32_t* __restr
   if (skip) skip[b] = g <= (double)delta ? 1 : 0;
 }
 
-// 1024 threads a sequence for a few of them (4 x 4224 tokens: 6.9 us with 256
-// threads and a token at a time, 4.3 now), 256 where many fill the chip.
+// 1024 threads a sequence and four tokens each per step for long sequences, else
+// 256 and one. Whole call at d 256, us, 256 and 1024 threads: 1 x 500 tokens 5.7
+// and 6.3, 1 x 1500 6.8 and 7.0, 4 x 1500 8.8 and 8.7, 4 x 2000 10.0 and 9.9, 4 x
+// 4224 15.7 and 13.8, 1 x 65536 94 and 52; more sequences than CUs lose: 512 x 500
+// 103.3 and 105.5.
+constexpr int kWideGap = 1536;
+
 hipError_t launch_gap(const float* cos_tok, const int32_t* seq_offsets, int B, int T, const int32_t* token_pos,
                       float delta, float* rho_all, float* rho_ret, float* gap, uint8_t* skip, hipStream_t stream) {
-  if (B <= kWideBatch)
-    hipLaunchKernelGGL(gap_kernel<1024>, dim3(B), dim3(1024), 0, stream, seq_offsets, T, token_pos, cos_tok, delta,
+  if (wide_signal(B, T, kWideGap))
+    hipLaunchKernelGGL((gap_kernel<1024, 4>), dim3(B), dim3(1024), 0, stream, seq_offsets, T, token_pos, cos_tok, delta,
                        rho_all, rho_ret, gap, skip);
   else
-    hipLaunchKernelGGL(gap_kernel<256>, dim3(B), dim3(256), 0, stream, seq_offsets, T, token_pos, cos_tok, delta,
+    hipLaunchKernelGGL((gap_kernel<256, 1>), dim3(B), dim3(256), 0, stream, seq_offsets, T, token_pos, cos_tok, delta,
                        rho_all, rho_ret, gap, skip);
   return hipGetLastError();
 }

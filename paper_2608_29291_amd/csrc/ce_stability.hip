@@ -171,10 +171,13 @@ hipError_t launch_stability(const int32_t* seq_offsets, const uint8_t* flags, in
                             const int32_t* tp_t, const int32_t* tp_ref, float* jaccard, float* j_rand,
                             float* rda, hipStream_t stream) {
   if (B <= 0) return hipSuccess;
-  // a few sequences leave the chip to themselves: 1024 threads each (4 x 4224
-  // tokens: 18.3 us with 256 threads and nine lgammas, 9.8 now); many fill it
-  // with 256
-  if (B <= kWideBatch)
+  // 1024 threads each only for long sequences: the lgammas of a wider workgroup
+  // cost more than its shorter loops save. us, 256 and 1024 threads: 4 x 500
+  // tokens 6.5 and 8.4, 4 x 2000 8.0 and 9.1, 4 x 4224 9.8 and 9.6, 1 x 16384 15.7
+  // and 12.1, 1 x 65536 34 and 22; two to a CU, 512 x 500: 7.9 and 16 (one token a
+  // step and nine lgammas a thread: 9.3, 10.7, 13, 25, 73 and 12)
+  constexpr int kWide = 4096;
+  if (wide_signal(B, T, kWide))
     hipLaunchKernelGGL(stability_kernel<1024>, dim3(B), dim3(1024), 0, stream, seq_offsets, flags, T, tp_t, tp_ref,
                        jaccard, j_rand, rda);
   else
