@@ -53,10 +53,16 @@ struct DecodeArgs {
   int B, H, Hkv, q_cap, kv_cap, causal;
   float scale_log2;
   int chunk;        // keys per work item (a multiple of 4 kKT)
-  int items;        // work items the grid and the workspace have room for
-  int32_t* first;   // [B] first item of each sequence that has several chunks
-  float* part;      // [items x Hkv x kRows x (kDh + 2)] output, maximum, sum
+  int items;        // work items the grid has room for
+  int part_rows;    // rows of a partial result
+  float* part;      // [slots x Hkv x part_rows x (kDh + 2)] output, maximum, sum
 };
+
+// Partial result of row r of chunk c of a sequence whose keys begin at klo
+// (its slots begin at 2 klo / chunk: see attention_split).
+__device__ __forceinline__ float* part_at(const DecodeArgs& a, int klo, int c, int kvh, int r) {
+  return a.part + (((int64_t)(2 * klo / a.chunk + c) * a.Hkv + kvh) * a.part_rows + r) * (kDh + 2);
+}
 
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
@@ -300,7 +306,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       x += *reinterpret_cast<const f32x4_t*>(ob + (w * kRows + r) * kOLd + d0);
     }
     if (cut) {
-      float* const p = a.part + (((int64_t)item * a.Hkv + kvh) * kRows + r) * (kDh + 2);
+      float* const p = part_at(a, klo, sub, kvh, r);
       *reinterpret_cast<u32x2_t*>(p + d0) = u32x2_t{__float_as_uint(x.x), __float_as_uint(x.y)};
       *reinterpret_cast<u32x2_t*>(p + d0 + 2) = u32x2_t{__float_as_uint(x.z), __float_as_uint(x.w)};
       if (d0 == 0) {
@@ -314,7 +320,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                    x.y * inv, x.z * inv, x.w * inv);
     }
   }
-  if (cut && sub == 0 && kvh == 0 && tid == 0) a.first[b] = item;
 }
 
 // Chunk results of the sequences that were cut, added in chunk order: a
@@ -324,19 +329,16 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(DecodeArgs a) {
   const int b = blockIdx.x, kvh = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = a.H / a.Hkv;
-  const int first_b = a.first[b];  // meaningful for cut sequences only
   const int lo = clampi(a.qo[b], 0, a.q_cap);
   const int nq = clampi(a.qo[b + 1], lo, a.q_cap) - lo;
   const int klo = clampi(a.ko[b], 0, a.kv_cap);
   const int nk = clampi(a.ko[b + 1], klo, a.kv_cap) - klo;
   const int rows = nq * g;
-  if (rows <= 0 || rows > kRows || nk <= a.chunk || nk > (int64_t)a.items * a.chunk) return;
+  if (rows <= 0 || rows > kRows || nk <= a.chunk) return;
   const int n = (nk + a.chunk - 1) / a.chunk;
-  const int64_t stride = (int64_t)a.Hkv * kRows * (kDh + 2);  // floats between chunks
-  // (offsets that overlap can count more items than there are: stay inside)
-  const int first = clampi(first_b, 0, max(0, a.items - n));
+  const int64_t stride = (int64_t)a.Hkv * a.part_rows * (kDh + 2);  // floats between chunks
   for (int r = wave; r < rows; r += 4) {
-    const float* const p = a.part + (((int64_t)first * a.Hkv + kvh) * kRows + r) * (kDh + 2);
+    const float* const p = part_at(a, klo, 0, kvh, r);
     float m = -__builtin_inff(), l = 0.0f, x0 = 0.0f, x1 = 0.0f;
     for (int c0 = 0; c0 < n; c0 += 8) {
       float mc[8], lc[8], y0[8], y1[8];
@@ -382,14 +384,12 @@ hipError_t launch_attention_decode(const char* q, const char* k, const char* v, 
                                    float scale, void* ws, hipStream_t stream) {
   if (q_cap <= 0) return hipSuccess;
   DecodeArgs args{q, k, v, o, q_offsets, kv_offsets, B, H, Hkv, q_cap, kv_cap, causal ? 1 : 0,
-                  scale * 1.4426950408889634f, 0, 0, nullptr, nullptr};
+                  scale * 1.4426950408889634f, 0, 0, 0, nullptr};
   AttnSplit sp = attention_split(B, H, Hkv, q_cap, kv_cap, ws != nullptr);
   args.chunk = sp.chunk;
   args.items = sp.items;
-  if (ws) {
-    args.first = static_cast<int32_t*>(ws);
-    args.part = reinterpret_cast<float*>(static_cast<char*>(ws) + sp.part_off);
-  }
+  args.part_rows = sp.part_rows;
+  args.part = static_cast<float*>(ws);
   hipLaunchKernelGGL(attention_decode_kernel, dim3(sp.items, Hkv), dim3(256), 0, stream, args);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !sp.cuts) return e;

@@ -62,10 +62,13 @@ AttnSplit attention_split(int B, int H, int Hkv, int q_cap, int kv_cap, bool wit
   // a sequence's keys or rows end in at most one partial item
   sp.items = (int)(kv_cap / chunk + (int64_t)q_cap * g / kAttnRows + B);
   sp.cuts = kv_cap > chunk;
-  if (sp.few && sp.cuts) {
-    sp.part_off = align_up((size_t)B * 4);
-    sp.bytes = sp.part_off + (size_t)sp.items * Hkv * kAttnRows * (128 + 2) * 4;
-  }
+  // A sequence that is cut has more keys than a chunk, so its ceil(nk / chunk)
+  // items are at most 2 nk / chunk: with its first key's 2 klo / chunk as its
+  // first slot no two sequences share one, and 2 kv_cap / chunk are enough for
+  // every batch, whatever the number of sequences.
+  sp.part_rows = (int)(q_cap * g < kAttnRows ? q_cap * g : kAttnRows);
+  if (sp.few && sp.cuts)
+    sp.bytes = align_up((size_t)(2 * (int64_t)kv_cap / chunk) * Hkv * sp.part_rows * (128 + 2) * 4);
   return sp;
 }
 

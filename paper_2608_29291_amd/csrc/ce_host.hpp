@@ -149,8 +149,8 @@ struct AttnSplit {
   int chunk;        // keys per work item
   int items;        // work items per key/value head, at most
   int cuts;         // 1 when a sequence can have more keys than a chunk
-  size_t part_off;  // workspace: int32 [B] first items, then the partial results
-  size_t bytes;     // workspace bytes (0: none needed)
+  int part_rows;    // (query, head) rows per partial result
+  size_t bytes;     // workspace: partial results of the sequences that are cut (0: none needed)
 };
 AttnSplit attention_split(int B, int H, int Hkv, int q_cap, int kv_cap, bool with_ws);
 

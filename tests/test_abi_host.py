@@ -337,6 +337,23 @@ def test_attention_validation(kw, ptrs, code):
     assert ce.lib.ce_routed_attention(None, FAKE, FAKE, FAKE, FAKE, None) == ce.CE_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("heads,kv_heads", [(28, 4), (12, 2), (32, 32), (32, 1)])
+@pytest.mark.parametrize("B", [1, 16, 256, 1024, 4096, 65535])
+def test_attention_workspace_does_not_grow_with_the_batch(B, heads, kv_heads):
+    """At most 1024 partial results of at most 32 rows of (output, maximum,
+    sum), whatever the batch and the caches."""
+    most = 1024 * 32 * 130 * 4
+    top = (1 << 31) // (kv_heads * 256) - 1  # the entry point's limit
+    for kv in (1, 128, 129, 1000, 16 * 2000, 100000, top // 2, top):
+        if B * heads * 256 >= 1 << 31 or kv > top:
+            continue
+        at = _attn(B=B, n_heads=heads, n_kv_heads=kv_heads, q_capacity=B, kv_capacity=kv)
+        need = ce.lib.ce_attention_workspace_size(ctypes.byref(at))
+        assert need % 256 == 0 and need <= most, (B, kv, need)
+        if kv <= 128:
+            assert need == 0  # one chunk
+
+
 def tiling(B, T, d, r_c, r_e, dtype=ce.CE_BF16):
     out = (ctypes.c_int32 * 2)()
     r = ce.lib.ce_score_tiling(ctypes.byref(_batch(B=B, T=T)), ctypes.byref(_scorer(d=d, r_c=r_c, r_e=r_e,

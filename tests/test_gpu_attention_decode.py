@@ -45,6 +45,8 @@ CASES = {
     # all queries in one sequence of many; more queries than keys
     "skewed": ([40] + [0] * 7 + [1] * 40, [600] + [9] * 7 + [35] * 40, 12, 2),
     "short_cache": ([3, 2], [1, 2], 12, 2),
+    # many sequences that are cut: two chunks of 128 keys and a bit, three, one
+    "cut": ([1] * 40, [129, 128, 257, 130] * 10, 28, 4),
     "many": ([1] * 600, [(7 * i) % 90 for i in range(600)], 4, 2),
 }
 
