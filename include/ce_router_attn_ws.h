@@ -21,7 +21,8 @@ extern "C" {
  *       aligned, contents on entry do not matter; NULL is ce_routed_attention.
  *       CE_ERR_WORKSPACE if it is short or misaligned.
  * ce_attention_workspace_size depends on the sizes in attn only (no device
- * pointer is read) and is 0 when no workspace is used.
+ * pointer is read), is at most 17 MB, and is 0 when no workspace is used or the
+ * call would refuse attn.
  */
 size_t ce_attention_workspace_size(const ce_attn* attn);
 int ce_routed_attention_ws(const ce_attn* attn, const void* q, const void* k, const void* v, void* o, void* ws,

@@ -389,7 +389,8 @@ size_t ce_attention_workspace_size(const ce_attn* at) {
   if (!at || at->B < 1 || at->n_heads < 1 || at->n_kv_heads < 1 || at->n_heads % at->n_kv_heads != 0 ||
       at->q_capacity < 0 || at->kv_capacity < 0)
     return 0;
-  // over the entry points' size limits: nothing to run
+  // what the entry points refuse: nothing to run
+  if (at->dtype != CE_BF16 || at->head_dim != 128) return 0;
   const int64_t lim = (int64_t)1 << 31;
   if ((int64_t)at->q_capacity * at->n_heads * 256 >= lim || (int64_t)at->kv_capacity * at->n_kv_heads * 256 >= lim)
     return 0;

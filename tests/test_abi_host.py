@@ -15,14 +15,15 @@ from ce_workloads import config_layout, build_layout, small_workload
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "ce_router.h")
+ATTN_WS_HEADER = os.path.join(ROOT, "include", "ce_router_attn_ws.h")
 
 ce = pytest.importorskip("paper_2608_29291_amd")
 
 FAKE = 0x10000  # never dereferenced: validation fails first
 
 
-def declared_functions():
-    txt = open(HEADER).read()
+def declared_functions(header=HEADER):
+    txt = open(header).read()
     txt = re.sub(r"/\*.*?\*/", "", txt, flags=re.S)
     return sorted(set(re.findall(r"\b(ce_[a-z_]+)\s*\(", txt)))
 
@@ -33,6 +34,13 @@ def test_every_declared_symbol_is_exported():
     for n in names:
         assert hasattr(ce.lib, n), n
     assert set(names) == set(ce.EXPORTED)
+
+
+def test_workspace_attention_is_exported():
+    names = declared_functions(ATTN_WS_HEADER)
+    assert names == ["ce_attention_workspace_size", "ce_routed_attention_ws"]
+    for n in names:
+        assert hasattr(ce.lib, n), n
 
 
 def test_version_and_status_strings():
@@ -335,6 +343,28 @@ def test_attention_validation(kw, ptrs, code):
     at = _attn(**kw)
     assert ce.lib.ce_routed_attention(ctypes.byref(at), p["q"], p["k"], p["v"], p["o"], None) == code
     assert ce.lib.ce_routed_attention(None, FAKE, FAKE, FAKE, FAKE, None) == ce.CE_ERR_INVALID_ARG
+
+
+def attn_ws(at, ws=FAKE, short=0):
+    need = ce.lib.ce_attention_workspace_size(ctypes.byref(at))
+    return ce.lib.ce_routed_attention_ws(ctypes.byref(at), FAKE, FAKE, FAKE, FAKE, ws, max(need - short, 0), None)
+
+
+def test_attention_ws_validation():
+    """A workspace that is short or misaligned, and what the call refuses,
+    for which the size is 0."""
+    long = dict(q_capacity=2, kv_capacity=4000)
+    assert ce.lib.ce_attention_workspace_size(ctypes.byref(_attn(**long))) > 0
+    assert attn_ws(_attn(**long), short=1) == ce.CE_ERR_WORKSPACE
+    assert attn_ws(_attn(**long), ws=FAKE + 8) == ce.CE_ERR_WORKSPACE
+    assert ce.lib.ce_routed_attention_ws(None, FAKE, FAKE, FAKE, FAKE, FAKE, 1 << 20, None) == ce.CE_ERR_INVALID_ARG
+    for kw, code in (({"B": 0}, ce.CE_ERR_INVALID_ARG), ({"n_kv_heads": 5}, ce.CE_ERR_INVALID_ARG),
+                     ({"q_capacity": -1}, ce.CE_ERR_INVALID_ARG), ({"head_dim": 64}, ce.CE_ERR_UNSUPPORTED),
+                     ({"dtype": ce.CE_F32}, ce.CE_ERR_UNSUPPORTED), ({"kv_capacity": 1 << 22}, ce.CE_ERR_UNSUPPORTED)):
+        at = _attn(**{**long, **kw})
+        assert ce.lib.ce_attention_workspace_size(ctypes.byref(at)) == 0, kw
+        assert attn_ws(at) == code, kw
+    assert ce.lib.ce_attention_workspace_size(None) == 0
 
 
 @pytest.mark.parametrize("heads,kv_heads", [(28, 4), (12, 2), (32, 32), (32, 1)])
