@@ -343,9 +343,11 @@ int attention_impl(const ce_attn* at, const void* q, const void* k, const void* 
   hipStream_t s = static_cast<hipStream_t>(stream);
   // Few queries (decode): the key/value heads' groups as rows, the keys cut;
   // else 128 queries of one head per workgroup (prefill, generation). The line
-  // lies where the sequences' rows fill one 32-column operand on average: a
-  // decode step is 90 us on the 128-query kernel and 21 us on the other, and
-  // above it the other would read the keys once more per 32 rows.
+  // lies where the sequences' rows fill one 32-column operand on average; the
+  // host sees no more of a batch, and the first kernel runs what it finds in a
+  // mixed one on the other's tiles. us, 28 / 4 heads, first and second: 16
+  // sequences of one query over 551 to 3100 keys 20.7 and 74, 8 of 4 queries over
+  // 2000 keys 19 and 41.
   if (sp.few)
     return hip_status(launch_attention_decode(cq, ck, cv, co, at->q_offsets, at->kv_offsets, at->B, at->n_heads,
                                               at->n_kv_heads, at->q_capacity, at->kv_capacity, at->causal != 0,

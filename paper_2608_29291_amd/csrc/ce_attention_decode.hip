@@ -19,14 +19,26 @@
 // The waves meet in LDS (their running maxima, sums and outputs); with more
 // than one chunk the fp32 results go to the workspace and a second launch
 // combines them in chunk order, so the result does not depend on which
-// workgroup finished first. A sequence with more than 32 rows is not cut.
+// workgroup finished first.
+//
+// The launch takes whole batches, chosen by their rows on average, so these may
+// come mixed with others: a sequence with several items' rows (a few more
+// queries) is cut into as many workgroups in all, its tiles of 32 rows times
+// longer chunks; a prefill runs the 128-query tiles of ce_attention_tile.hpp in
+// the same launch, which read its keys once per 128 queries. us, 28 / 4 heads,
+// (every sequence on 128-query tiles /) all in uncut tiles of 32 rows / now:
+// 1023 empty sequences and a prefill of 4681 (353 /) 610 / 244, 255 and one of
+// 1170 (45 /) 66 / 40, 255 of one query over 300 keys and a prefill of 915 (185 /)
+// 72 / 54, two sequences of 8000 keys with 5 queries and 1 (138 /) 238 / 37, 8 of
+// 2000 with 4 (41 /) 30 / 19, 64 queries over 8000 and 14 empty (181 /) 119 / 78,
+// 300 over 300 and 65 empty (14.4 /) 17.8 / 14.4.
 //
 // Measured (16 queries, 28 / 4 heads, caches of 551 to 3100 keys, 48 MB of keys
 // and values): 14.8 us + 5.8 us for the combination, 3.3 TB/s in the first
 // launch; the 128-query kernel took 90 us (one workgroup per query head walked
 // a whole cache, each key was read by the 7 heads of its group, and one row of
 // 128 was a query).
-#include "ce_device.hpp"
+#include "ce_attention_tile.hpp"
 #include "ce_host.hpp"
 #include "ce_launch.hpp"
 
@@ -34,44 +46,52 @@ namespace ce {
 
 namespace {
 
-constexpr int kDh = 128;
+using attn::clampi;
+using attn::kDh;
+using attn::kLazy;
+
 constexpr int kRowB = kDh * 2;           // bytes per key row and head
 constexpr int kRows = kAttnRows;         // (query, head) rows per work item
 constexpr int kKT = 32;                  // keys per tile of a wave
 constexpr int kVRow = kKT * 2;           // bytes per row of V^T
 constexpr int kVTile = kDh * kVRow;      // 8 KB
 constexpr int kOLd = kDh + 4;            // floats per row of the waves' outputs in LDS
-constexpr float kLazy = 8.0f;            // headroom of the running maximum (exponent of 2)
+// A sequence of kLongQ queries whose keys would be cut in fewer chunks than
+// kLongC takes 128-query tiles; its g per tile are then no more items than its
+// tiles of 32 rows, which the grid has room for. us, 28 / 4 heads, row tiles and
+// 128-query tiles: 64 queries over 64 keys 8.2 and 6.7, 32 over 1000 in two
+// chunks 29.6 and 24.2, 100 over 8000 in three 112 and 138, 32 over 8000 51 and
+// 139.
+constexpr int kLongQ = 32;
+constexpr int kLongC = 3;
 
-struct DecodeArgs {
-  const char* q;
-  const char* k;
-  const char* v;
-  char* o;
-  const int32_t* qo;
-  const int32_t* ko;
-  int B, H, Hkv, q_cap, kv_cap, causal;
-  float scale_log2;
+struct DecodeArgs : attn::AttnArgs {
   int chunk;        // keys per work item (a multiple of 4 kKT)
   int items;        // work items the grid has room for
   int part_rows;    // rows of a partial result
   float* part;      // [slots x Hkv x part_rows x (kDh + 2)] output, maximum, sum
 };
 
-// Partial result of row r of chunk c of a sequence whose keys begin at klo
+// Partial result of row r of item i of a sequence whose keys begin at klo
 // (its slots begin at 2 klo / chunk: see attention_split).
-__device__ __forceinline__ float* part_at(const DecodeArgs& a, int klo, int c, int kvh, int r) {
-  return a.part + (((int64_t)(2 * klo / a.chunk + c) * a.Hkv + kvh) * a.part_rows + r) * (kDh + 2);
+__device__ __forceinline__ float* part_at(const DecodeArgs& a, int klo, int i, int kvh, int r) {
+  return a.part + (((int64_t)(2 * klo / a.chunk + i) * a.Hkv + kvh) * a.part_rows + r) * (kDh + 2);
 }
 
-__device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
-
-// Work items of a sequence with `rows` (query, head) rows and nk keys: its
-// chunks of keys, or its tiles of 32 rows when there are several.
-__device__ __forceinline__ int items_of(int rows, int nk, int chunk) {
-  if (rows <= 0) return 0;
-  if (rows > kRows) return (rows + kRows - 1) / kRows;
-  return nk <= chunk ? 1 : (nk + chunk - 1) / chunk;
+// How a sequence of nq queries (g rows each) and nk keys is cut: T tiles of 32
+// rows times C chunks of T a.chunk keys, or 128-query tiles of one head each.
+struct Cut {
+  bool by_query;
+  int T, C, n_items;
+};
+__device__ __forceinline__ Cut cut_of(int nq, int g, int nk, int chunk) {
+  Cut c = {false, (nq * g + kRows - 1) / kRows, 1, 0};
+  if (nk > chunk) c.C = (nk + chunk - 1) / chunk;
+  if (c.T > 1) c.C = (c.C + c.T - 1) / c.T;
+  c.by_query = c.T > 1 && nq >= kLongQ && c.C < kLongC;
+  if (c.by_query) c.C = 1;
+  c.n_items = c.by_query ? (nq + attn::kQT - 1) / attn::kQT * g : c.T * c.C;
+  return c;
 }
 
 // Byte offset of unit u (4 keys) of V^T row d in a wave's tile. A write covers
@@ -83,10 +103,10 @@ __device__ __forceinline__ uint32_t vt_off(int d, uint32_t u) {
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attention_decode_kernel(
     DecodeArgs a) {
-  __shared__ __attribute__((aligned(16))) char smem[4 * kRows * kOLd * 4];  // V^T tiles, then outputs
+  __shared__ __attribute__((aligned(1024))) char smem[4 * kRows * kOLd * 4];  // V^T tiles, then outputs
   __shared__ float ml[2][4][kRows];
   __shared__ int wsh[8];
-  static_assert(4 * kRows * kOLd * 4 >= 4 * kVTile, "the V tiles fit");
+  static_assert(4 * kRows * kOLd * 4 >= 4 * kVTile && 4 * kRows * kOLd * 4 >= 4 * attn::kKBytes, "the tiles fit");
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -108,7 +128,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       nq = clampi(q1, lo, a.q_cap) - lo;
       klo = clampi(k0, 0, a.kv_cap);
       nk = clampi(k1, klo, a.kv_cap) - klo;
-      n = items_of(nq * g, nk, a.chunk);
+      n = cut_of(nq, g, nk, a.chunk).n_items;
     }
     int x = n;
 #pragma unroll
@@ -145,12 +165,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int nq = __builtin_amdgcn_readfirstlane(wsh[3]);
   const int klo = __builtin_amdgcn_readfirstlane(wsh[4]);
   const int nk = __builtin_amdgcn_readfirstlane(wsh[5]);
-  const int rows_all = nq * g;
-  const bool cut = rows_all <= kRows && nk > a.chunk;
-  const int r0 = rows_all > kRows ? sub * kRows : 0;
-  const int rows = min(kRows, rows_all - r0);
-  const int kbeg = cut ? sub * a.chunk : 0;
-  const int kend = cut ? min(nk, kbeg + a.chunk) : nk;
+  const Cut ct = cut_of(nq, g, nk, a.chunk);
+  if (ct.by_query) {
+    // the workgroups of one x, which share an XCD (the grid's x is a multiple of
+    // its count), take heads of one key/value head as far as they go; last tiles
+    // first: under a causal mask they see the most keys
+    const int u = sub * a.Hkv + kvh;
+    const int tile = (nq + attn::kQT - 1) / attn::kQT - 1 - u / a.H;
+    attn::attention_tile<true>(a, smem, b, u % a.H, tile * attn::kQT, nq, qbase);
+    return;
+  }
+  const bool cut = ct.C > 1;
+  const int tile = sub / ct.C;
+  const int r0 = tile * kRows;
+  const int rows = min(kRows, nq * g - r0);
+  const int kbeg = (sub - tile * ct.C) * (cut ? a.chunk * ct.T : 0);
+  const int kend = cut ? min(nk, kbeg + a.chunk * ct.T) : nk;
   const int off = nk - nq;  // end alignment of the causal mask
 
   // ---- the query row of this lane, K-chunks of (lane / 32) ----
@@ -322,9 +352,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
-// Chunk results of the sequences that were cut, added in chunk order: a
-// workgroup per sequence and key/value head, a wave per row (4 at a time),
-// two dims per lane; eight chunks' loads in flight.
+// Chunk results of the sequences that were cut, added in chunk order:
+// workgroups per sequence and key/value head, a wave per row (4 at a time and
+// workgroup), two dims per lane; eight chunks' loads in flight.
 __global__ __launch_bounds__(256) void attention_combine_kernel(DecodeArgs a) {
   const int b = blockIdx.x, kvh = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -333,12 +363,12 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(DecodeArgs a) {
   const int nq = clampi(a.qo[b + 1], lo, a.q_cap) - lo;
   const int klo = clampi(a.ko[b], 0, a.kv_cap);
   const int nk = clampi(a.ko[b + 1], klo, a.kv_cap) - klo;
-  const int rows = nq * g;
-  if (rows <= 0 || rows > kRows || nk <= a.chunk) return;
-  const int n = (nk + a.chunk - 1) / a.chunk;
+  const Cut ct = cut_of(nq, g, nk, a.chunk);
+  if (nq <= 0 || ct.C <= 1) return;
+  const int rows = nq * g, n = ct.C;
   const int64_t stride = (int64_t)a.Hkv * a.part_rows * (kDh + 2);  // floats between chunks
-  for (int r = wave; r < rows; r += 4) {
-    const float* const p = part_at(a, klo, 0, kvh, r);
+  for (int r = wave + 4 * (int)blockIdx.z; r < rows; r += 4 * (int)gridDim.z) {
+    const float* const p = part_at(a, klo, r / kRows * n, kvh, r % kRows);
     float m = -__builtin_inff(), l = 0.0f, x0 = 0.0f, x1 = 0.0f;
     for (int c0 = 0; c0 < n; c0 += 8) {
       float mc[8], lc[8], y0[8], y1[8];
@@ -383,17 +413,22 @@ hipError_t launch_attention_decode(const char* q, const char* k, const char* v, 
                                    const int32_t* kv_offsets, int B, int H, int Hkv, int q_cap, int kv_cap, bool causal,
                                    float scale, void* ws, hipStream_t stream) {
   if (q_cap <= 0) return hipSuccess;
-  DecodeArgs args{q, k, v, o, q_offsets, kv_offsets, B, H, Hkv, q_cap, kv_cap, causal ? 1 : 0,
-                  scale * 1.4426950408889634f, 0, 0, 0, nullptr};
+  DecodeArgs args{{q, k, v, o, q_offsets, kv_offsets, B, H, Hkv, q_cap, kv_cap, causal ? 1 : 0,
+                   scale * 1.4426950408889634f}, 0, 0, 0, nullptr};
   AttnSplit sp = attention_split(B, H, Hkv, q_cap, kv_cap, ws != nullptr);
   args.chunk = sp.chunk;
   args.items = sp.items;
   args.part_rows = sp.part_rows;
   args.part = static_cast<float*>(ws);
-  hipLaunchKernelGGL(attention_decode_kernel, dim3(sp.items, Hkv), dim3(256), 0, stream, args);
+  const int items = (sp.items + kXcdCount - 1) / kXcdCount * kXcdCount;
+  hipLaunchKernelGGL(attention_decode_kernel, dim3(items, Hkv), dim3(256), 0, stream, args);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !sp.cuts) return e;
-  hipLaunchKernelGGL(attention_combine_kernel, dim3(B, Hkv), dim3(256), 0, stream, args);
+  // a sequence may have several tiles of rows when there are more queries than
+  // sequences (else one would have to be empty for each query more)
+  const int g = H / Hkv;
+  const int tiles = q_cap <= B ? 1 : ((q_cap < kLongQ ? q_cap : kLongQ - 1) * g + kRows - 1) / kRows;
+  hipLaunchKernelGGL(attention_combine_kernel, dim3(B, Hkv, tiles < 8 ? tiles : 8), dim3(256), 0, stream, args);
   return hipGetLastError();
 }
 

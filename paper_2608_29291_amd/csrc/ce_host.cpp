@@ -59,11 +59,13 @@ AttnSplit attention_split(int B, int H, int Hkv, int q_cap, int kv_cap, bool wit
   if (chunk < 128) chunk = 128;
   if (!with_ws) chunk = (int64_t)1 << 30;
   sp.chunk = (int)chunk;
-  // a sequence's keys or rows end in at most one partial item
+  // items of a sequence: T tiles of its rows (at most rows / kAttnRows + 1) times
+  // ceil(nk / (T chunk)) <= nk / (T chunk) + 1, together at most nk / chunk +
+  // rows / kAttnRows + 1; a long one's 128-query tiles are fewer than its T
   sp.items = (int)(kv_cap / chunk + (int64_t)q_cap * g / kAttnRows + B);
   sp.cuts = kv_cap > chunk;
-  // A sequence that is cut has more keys than a chunk, so its ceil(nk / chunk)
-  // items are at most 2 nk / chunk: with its first key's 2 klo / chunk as its
+  // A sequence that is cut has more than T chunk keys, so its items, at most nk /
+  // chunk + T, are at most 2 nk / chunk: with its first key's 2 klo / chunk as its
   // first slot no two sequences share one, and 2 kv_cap / chunk are enough for
   // every batch, whatever the number of sequences.
   sp.part_rows = (int)(q_cap * g < kAttnRows ? q_cap * g : kAttnRows);

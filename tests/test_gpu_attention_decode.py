@@ -45,6 +45,15 @@ CASES = {
     # all queries in one sequence of many; more queries than keys
     "skewed": ([40] + [0] * 7 + [1] * 40, [600] + [9] * 7 + [35] * 40, 12, 2),
     "short_cache": ([3, 2], [1, 2], 12, 2),
+    # mixed batches: a prefill among decode steps and empty sequences; sequences
+    # of 2 to 7 tiles of rows over long caches (tiles times chunks); around the
+    # line to 128-query tiles (32 queries), cut and not, one row per query and odd
+    "prefill": ([260] + [1] * 30 + [0] * 35, [260] + [700] * 30 + [5] * 35, 28, 4),
+    "tiles": ([5, 1, 15, 31] + [0] * 8, [3000, 900, 1500, 4001] + [0] * 8, 28, 4),
+    "line": ([31, 32, 33] + [0] * 20, [700, 699, 701] + [3] * 20, 28, 4),
+    "line_cut": ([33, 32] + [0] * 13, [4001, 2500] + [3] * 13, 12, 2),
+    "ungrouped_line": ([40, 33, 1], [2000, 100, 200], 4, 4),
+    "odd_group": ([129, 2] + [0] * 20, [200, 3000] + [0] * 20, 20, 4),
     # many sequences that are cut: two chunks of 128 keys and a bit, three, one
     "cut": ([1] * 40, [129, 128, 257, 130] * 10, 28, 4),
     "many": ([1] * 600, [(7 * i) % 90 for i in range(600)], 4, 2),
