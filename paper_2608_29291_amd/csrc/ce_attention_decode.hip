@@ -176,7 +176,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     return;
   }
   const bool cut = ct.C > 1;
-  const int tile = sub / ct.C;
+  const int tile = ct.T == 1 ? 0 : ct.C == 1 ? sub : sub / ct.C;
   const int r0 = tile * kRows;
   const int rows = min(kRows, nq * g - r0);
   const int kbeg = (sub - tile * ct.C) * (cut ? a.chunk * ct.T : 0);

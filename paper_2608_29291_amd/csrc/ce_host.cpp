@@ -56,7 +56,12 @@ AttnSplit attention_split(int B, int H, int Hkv, int q_cap, int kv_cap, bool wit
   const int64_t target = 2 * kXcdCount * kCusPerXcd;
   int64_t chunk = ((int64_t)kv_cap * Hkv + target - 1) / target;
   chunk = (chunk + 127) / 128 * 128;
-  if (chunk < 128) chunk = 128;
+  // Short caches: a cut saves less than the launch that adds it up. us, cut at
+  // 128 keys / at this (28 / 4 heads): 1 x 200 keys 10.7 / 8.5, 1 x 300 11.1 / 10.1,
+  // 3 x 128 8.8 / 7.3, 8 x 40 7.8 / 6.3, 8 x 200 11.0 / 10.1, 32 x 200 13.8 / 10.5;
+  // 1 x 500 whole 12.2, cut 11.0, and 8 x 300 at 256 keys 13.2, at 128 11.8.
+  const int64_t least = kv_cap <= 384 ? 384 : kv_cap <= (int64_t)256 * B ? 256 : 128;
+  if (chunk < least) chunk = least;
   if (!with_ws) chunk = (int64_t)1 << 30;
   sp.chunk = (int)chunk;
   // items of a sequence: T tiles of its rows (at most rows / kAttnRows + 1) times

@@ -141,9 +141,9 @@ int score_tiling(int B, int T, int d, int r_core, int r_exp, int elem, int* tm, 
 // `few` says that the sequences' rows fit a work item of kAttnRows on average.
 // Keys are cut into chunks so that about two workgroups run on each of the 256
 // CUs (few enough that all are resident, so the whole cache is in flight), of
-// at least 128 keys, one tile of 32 for each wave of a workgroup; a sequence of
-// T such items' rows in chunks T times as long. Without a workspace no sequence
-// is cut.
+// at least 128 keys (one tile of 32 for each wave of a workgroup; more where the
+// caches are short); a sequence of T such items' rows in chunks T times as long.
+// Without a workspace no sequence is cut.
 constexpr int kAttnRows = 32;
 struct AttnSplit {
   int few;          // 1: this kernel's shape of call

@@ -56,6 +56,12 @@ CASES = {
     "odd_group": ([129, 2] + [0] * 20, [200, 3000] + [0] * 20, 20, 4),
     # many sequences that are cut: two chunks of 128 keys and a bit, three, one
     "cut": ([1] * 40, [129, 128, 257, 130] * 10, 28, 4),
+    # the same at chunks of 128 keys (256 where caches are that short on average),
+    # and the line below which nothing is cut
+    "edges_128": ([1] * 9, [1, 128, 129, 255, 256, 257, 384, 385, 1500], 12, 2),
+    "cut_128": ([1] * 41, [129, 128, 257, 130] * 10 + [6000], 28, 4),
+    "one_whole": ([1], [384], 12, 2),
+    "one_cut": ([1], [385], 12, 2),
     "many": ([1] * 600, [(7 * i) % 90 for i in range(600)], 4, 2),
 }
 
