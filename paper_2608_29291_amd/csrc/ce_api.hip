@@ -249,17 +249,19 @@ int routed_block_impl(const ce_batch* batch, const void* hidden_in, void* hidden
   FfnGemmArgs dn = down_args(ffn, batch, act, nullptr, static_cast<char*>(hidden_out), grp,
                              kept_idx, static_cast<const char*>(hidden_in), kt, n0);
   set_split(dn, ws, L, 1);
+  const FfnRoute rd = ffn_route(dn, 1, bf16);
   double* gap_part = go ? at<double>(ws, L.gap_part) : nullptr;
   if (go) {
     dn.gap_part = gap_part;
-    dn.gap_np = ffn_down_gap_slots(dn, bf16);
+    dn.gap_np = ffn_down_gap_slots(dn, rd, bf16);
   }
   FfnGemmArgs g = gateup_args(ffn, batch, static_cast<const char*>(hidden_in), grp, kept_idx, act,
                               nullptr, kt, n0);
   set_split(g, ws, L, 0);
-  g.clear_n = ffn_split_counters(dn, 1, bf16);
+  const FfnRoute rg = ffn_route(g, 0, bf16);
+  g.clear_n = ffn_split_counters(rd);
   g.clear_cnt = g.clear_n > 0 ? dn.tile_cnt : nullptr;
-  const int gu_counters = ffn_split_counters(g, 0, bf16);
+  const int gu_counters = ffn_split_counters(rg);
 
   // 2-3. per-sequence TopK + packed index maps (Eq. 6); the select launch
   //      also clears the gate/up launch's arrival counters
@@ -294,7 +296,7 @@ int routed_block_impl(const ce_batch* batch, const void* hidden_in, void* hidden
     const int blocks = (batch->T + kCopyRows - 1) / kCopyRows;
     const BypassCopy copy{static_cast<const char*>(hidden_in), static_cast<char*>(hidden_out),
                           (int64_t)ffn->d * elem, batch->T, token_pos, blocks < 1024 ? blocks : 1024, 0};
-    if (batch->kept_capacity > 0 && gateup_takes_copy(g, bf16))
+    if (batch->kept_capacity > 0 && gateup_takes_copy(rg))
       g.copy = copy;
     else
       CE_TRY(launch_copy_rows(copy.src, copy.dst, copy.row_bytes, batch->T, token_pos, s));
@@ -312,9 +314,9 @@ int routed_block_impl(const ce_batch* batch, const void* hidden_in, void* hidden
   if (ffn->n_sets == 2)
     CE_TRY(launch_group(kept_idx, kept_off, batch->B, batch->kept_capacity, batch->T, batch->flags,
                         grp, n0, s));
-  CE_TRY(launch_ffn_gateup(g, bf16, s, gu_counters > 0));
+  CE_TRY(launch_ffn_gateup(g, rg, bf16, s, gu_counters > 0));
   // 5. down projection + residual, scattered straight into the token rows
-  CE_TRY(launch_ffn_down(dn, bf16, s, g.clear_cnt != nullptr));
+  CE_TRY(launch_ffn_down(dn, rd, bf16, s, g.clear_cnt != nullptr));
   return finish_gap();
 }
 
@@ -423,7 +425,8 @@ int ce_ffn_gateup(const ce_batch* batch, const void* compact, const int32_t* kep
   FfnGemmArgs g = gateup_args(w, batch, static_cast<const char*>(compact), grp, nullptr,
                               static_cast<char*>(act), grp, kept_offsets + batch->B, n0);
   set_split(g, ws, L, 0);
-  CE_TRY(launch_ffn_gateup(g, w->dtype == CE_BF16, s));
+  const bool bf16 = w->dtype == CE_BF16;
+  CE_TRY(launch_ffn_gateup(g, ffn_route(g, 0, bf16), bf16, s));
   return CE_OK;
 }
 
@@ -440,7 +443,8 @@ int ce_ffn_down(const ce_batch* batch, const void* act, const int32_t* kept_idx,
                              static_cast<char*>(ffn_out), grp, nullptr, nullptr,
                              kept_offsets + batch->B, n0);
   set_split(dn, ws, L, 1);
-  CE_TRY(launch_ffn_down(dn, w->dtype == CE_BF16, s));
+  const bool bf16 = w->dtype == CE_BF16;
+  CE_TRY(launch_ffn_down(dn, ffn_route(dn, 1, bf16), bf16, s));
   return CE_OK;
 }
 
@@ -464,10 +468,11 @@ int ce_routed_ffn(const ce_batch* batch, const void* compact, const int32_t* kep
   FfnGemmArgs g = gateup_args(w, batch, static_cast<const char*>(compact), grp, nullptr, act,
                               nullptr, kt, n0);
   set_split(g, ws, L, 0);
-  g.clear_n = ffn_split_counters(dn, 1, bf16);
+  const FfnRoute rg = ffn_route(g, 0, bf16), rd = ffn_route(dn, 1, bf16);
+  g.clear_n = ffn_split_counters(rd);
   g.clear_cnt = g.clear_n > 0 ? dn.tile_cnt : nullptr;
-  CE_TRY(launch_ffn_gateup(g, bf16, s));
-  CE_TRY(launch_ffn_down(dn, bf16, s, g.clear_cnt != nullptr));
+  CE_TRY(launch_ffn_gateup(g, rg, bf16, s));
+  CE_TRY(launch_ffn_down(dn, rd, bf16, s, g.clear_cnt != nullptr));
   return CE_OK;
 }
 
@@ -512,15 +517,16 @@ int ce_routed_ffn_pruned(const ce_batch* batch, const void* compact, const int32
   if (w->n_sets == 2)
     CE_TRY(launch_group(kept_idx, kept_offsets, batch->B, batch->kept_capacity, batch->T, batch->flags, grp, n0,
                         s));
-  g.clear_n = ffn_split_counters(dn, 1, true);
+  const FfnRoute rg = ffn_route(g, 0, true), rd = ffn_route(dn, 1, true);
+  g.clear_n = ffn_split_counters(rd);
   g.clear_cnt = g.clear_n > 0 ? dn.tile_cnt : nullptr;
   // 1. gate/up + SwiGLU, with the per-segment |z| sums
-  CE_TRY(launch_ffn_gateup(g, true, s));
+  CE_TRY(launch_ffn_gateup(g, rg, true, s));
   // 2. saliency (Eq. 8), leakage (Eq. 9) and the pruned/full choice per sequence
   CE_TRY(launch_saliency_segments(g, kept_offsets, norms, batch->B, n_keep, delta, chunk_tot, saliency, leakage,
                                   use_pruned, row_flag, seq_cnt, s));
   // 3. down, skipping the channels of P on the rows that run pruned
-  CE_TRY(launch_ffn_down_pruned(dn, s, g.clear_cnt != nullptr));
+  CE_TRY(launch_ffn_down(dn, rd, true, s, g.clear_cnt != nullptr));
   return CE_OK;
 }
 
@@ -649,6 +655,38 @@ int ce_routed_attention(const ce_attn* at, const void* q, const void* k, const v
 int ce_routed_attention_ws(const ce_attn* at, const void* q, const void* k, const void* v, void* o, void* ws,
                            size_t ws_bytes, void* stream) {
   return attention_impl(at, q, k, v, o, ws, ws_bytes, stream);
+}
+
+// For tests and tuning: the route of the FFN launches over `cap` packed rows,
+// mode 0 = gate/up, 1 = down; out = {FfnKernel, weight blocks and token blocks of
+// the mid-size tile, pieces over K (mid-size or split tiles), absorb}.
+int ce_ffn_route(int mode, int32_t cap, int32_t d, int32_t d_ff, int32_t n_sets, int dtype, int pruned,
+                 int32_t out[5]) {
+  const int elem = elem_size(dtype);
+  if (!out || mode < 0 || mode > 1 || cap < 1 || d < 1 || d_ff < 1 || n_sets < 1 || n_sets > 2 || elem == 0)
+    return CE_ERR_INVALID_ARG;
+  ce_batch b = {};
+  b.B = 1;
+  b.T = b.kept_capacity = cap;
+  ce_ffn_w w = {};
+  w.d = d;
+  w.d_ff = d_ff;
+  w.n_sets = n_sets;
+  w.dtype = dtype;
+  const WsLayout L = ws_layout(pruned ? CE_WS_FFN_PRUNED : CE_WS_FFN, 1, cap, cap, d, d_ff, elem);
+  char* const base = reinterpret_cast<char*>(L.total);  // never dereferenced
+  FfnGemmArgs a = mode == 0 ? gateup_args(&w, &b, base, nullptr, nullptr, base, nullptr, nullptr, nullptr)
+                            : down_args(&w, &b, base, nullptr, base, nullptr, nullptr, nullptr, nullptr, nullptr);
+  set_split(a, base, L, mode);
+  if (pruned && mode == 0) a.sal_part = reinterpret_cast<float*>(base);
+  if (pruned && mode == 1) a.row_flag = reinterpret_cast<const uint8_t*>(base);
+  const FfnRoute r = ffn_route(a, mode, dtype == CE_BF16);
+  out[0] = r.kernel;
+  out[1] = r.kernel == kFfnMid ? r.mid.wb : 0;
+  out[2] = r.kernel == kFfnMid ? r.mid.m : 0;
+  out[3] = r.kernel == kFfnMid ? r.mid.pieces : r.kernel == kFfnWide ? r.split.pieces : 1;
+  out[4] = r.kernel == kFfnWide ? r.split.absorb : 0;
+  return CE_OK;
 }
 
 }  // extern "C"

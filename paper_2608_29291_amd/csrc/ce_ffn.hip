@@ -1304,82 +1304,63 @@ inline MidPlan mid_of(const FfnGemmArgs& a, int mode) {
   return p;
 }
 
-hipError_t launch_ffn_gateup(const FfnGemmArgs& a, bool bf16, hipStream_t stream, bool counters_clear) {
-  if (bf16) {
-    const MidPlan mp = mid_of(a, 0);
-    if (few_ok(a) || mp.use) {
-      const hipError_t e = mp.use ? launch_ffn_mid(a, 0, mp, stream) : launch_ffn_few(a, 0, true, stream);
-      return e == hipSuccess && a.sal_part ? launch_segment_sums(a, stream) : e;
-    }
-    if (pp2_ok(a)) {
-      int n_tt, n_ft;
-      const GemmSplit sp = pp2_plan<0>(a, &n_tt, &n_ft);
-      return launch_pp2<0, 8, true>(a, sp, n_tt, n_ft, stream, counters_clear);
-    }
-    return launch_cfg<true, 0, 256, 256, 4, 2, 1, 1, 4>(a, stream);
+FfnRoute ffn_route(const FfnGemmArgs& a, int mode, bool bf16) {
+  FfnRoute r = {};
+  if (!bf16) {
+    if (few32_ok(a, mode)) r.kernel = kFfnFew;
+    return r;
   }
-  if (few32_ok(a, 0)) return launch_ffn_few(a, 0, false, stream);
-  if (!big_ok(a) && grid_tiles(a, 64, 128) < 128) return launch_cfg<false, 0, 64, 64, 1, 2, 2>(a, stream);
-  return launch_cfg<false, 0, 128, 128, 2, 2, 2>(a, stream);
+  if (few_ok(a)) {
+    r.kernel = kFfnFew;
+    return r;
+  }
+  r.mid = mid_of(a, mode);
+  if (r.mid.use) {
+    r.kernel = kFfnMid;
+    return r;
+  }
+  if (!pp2_ok(a)) return r;
+  r.split = mode == 0 ? pp2_plan<0>(a, &r.n_tt, &r.n_ft) : pp2_plan<1>(a, &r.n_tt, &r.n_ft);
+  // down runs on these tiles when they split or number >= 200, or to prune
+  if (mode == 0 || a.row_flag || r.split.pieces > 1 || (int64_t)r.n_tt * r.n_ft >= 200) r.kernel = kFfnWide;
+  return r;
 }
 
-// the down GEMM runs on the ping-pong kernel when it splits or has >= 200 tiles
-inline bool down_on_pp2(const FfnGemmArgs& a, const GemmSplit& sp, int n_tt, int n_ft) {
-  return pp2_ok(a) && (sp.pieces > 1 || (int64_t)n_tt * n_ft >= 200);
-}
-
-int ffn_split_counters(const FfnGemmArgs& a, int mode, bool bf16) {
-  if (!bf16 || !pp2_ok(a) || few_ok(a) || mid_of(a, mode).use || !a.part || !a.tile_cnt) return 0;
-  int n_tt, n_ft;
-  const GemmSplit sp = mode == 0 ? pp2_plan<0>(a, &n_tt, &n_ft) : pp2_plan<1>(a, &n_tt, &n_ft);
-  if (mode == 1 && !down_on_pp2(a, sp, n_tt, n_ft)) return 0;
-  return sp.pieces > 1 ? kXcds * sp.tail_x : 0;
-}
-
-bool gateup_takes_copy(const FfnGemmArgs& g, bool bf16) {
-  return !bf16 || !pp2_ok(g) || few_ok(g) || mid_of(g, 0).use;
+hipError_t launch_ffn_gateup(const FfnGemmArgs& a, const FfnRoute& r, bool bf16, hipStream_t stream,
+                             bool counters_clear) {
+  if (r.kernel == kFfnWide) return launch_pp2<0, 8, true>(a, r.split, r.n_tt, r.n_ft, stream, counters_clear);
+  if (r.kernel == kFfnTiles)
+    return bf16 ? launch_cfg<true, 0, 256, 256, 4, 2, 1, 1, 4>(a, stream)
+                : launch_cfg<false, 0, 128, 128, 2, 2, 2>(a, stream);
+  const hipError_t e = r.kernel == kFfnMid ? launch_ffn_mid(a, 0, r.mid, stream) : launch_ffn_few(a, 0, bf16, stream);
+  return e == hipSuccess && a.sal_part ? launch_segment_sums(a, stream) : e;
 }
 
 bool ffn_pruned_ok(const FfnGemmArgs& g, const FfnGemmArgs& dn) { return pp2_ok(g) && pp2_ok(dn); }
 
-hipError_t launch_ffn_down_pruned(const FfnGemmArgs& a, hipStream_t stream, bool counters_clear) {
-  if (few_ok(a)) return launch_ffn_few(a, 1, true, stream);
-  const MidPlan mp = mid_of(a, 1);
-  if (mp.use) return launch_ffn_mid(a, 1, mp, stream);
-  int n_tt, n_ft;
-  const GemmSplit sp = pp2_plan<1>(a, &n_tt, &n_ft);
-  return launch_pp2<1, 8, true, 2, true, true, true>(a, sp, n_tt, n_ft, stream, counters_clear);
+int ffn_down_gap_slots(const FfnGemmArgs& a, const FfnRoute& r, bool bf16) {
+  int f;  // output features per slot
+  if (r.kernel == kFfnFew) f = kFewGapFeatures;
+  else if (r.kernel == kFfnMid) f = a.n_feat;  // one slot per row
+  else if (r.kernel == kFfnWide) f = 128;
+  else if (bf16) f = 64;  // 256 x 128 tiles on 4 x 2 waves, 128 x 128 on 2 x 2
+  else f = grid_tiles(a, 128, 128) < 128 ? 32 : 64;
+  return (a.n_feat + f - 1) / f;
 }
 
-int ffn_down_gap_slots(const FfnGemmArgs& a, bool bf16) {
-  int fpw;  // output features per slot of the kernel launch_ffn_down picks
-  if (bf16 && few_ok(a)) {
-    fpw = kFewGapFeatures;
-  } else if (bf16 && mid_of(a, 1).use) {
-    fpw = a.n_feat;  // one slot per row
-  } else if (bf16) {
-    int n_tt, n_ft;
-    const GemmSplit sp = pp2_plan<1>(a, &n_tt, &n_ft);
-    if (down_on_pp2(a, sp, n_tt, n_ft)) fpw = 128;
-    else fpw = 64;  // 256 x 128 tiles on 4 x 2 waves, 128 x 128 on 2 x 2
-  } else {
-    fpw = few32_ok(a, 1) ? kFewGapFeatures : grid_tiles(a, 128, 128) < 128 ? 32 : 64;
+hipError_t launch_ffn_down(const FfnGemmArgs& a, const FfnRoute& r, bool bf16, hipStream_t stream,
+                           bool counters_clear) {
+  if (r.kernel == kFfnFew) return launch_ffn_few(a, 1, bf16, stream);
+  if (r.kernel == kFfnMid) return launch_ffn_mid(a, 1, r.mid, stream);
+  if (r.kernel == kFfnWide) {
+    if (a.row_flag)
+      return launch_pp2<1, 8, true, 2, true, true, true>(a, r.split, r.n_tt, r.n_ft, stream, counters_clear);
+    return launch_pp2<1, 8, true>(a, r.split, r.n_tt, r.n_ft, stream, counters_clear);
   }
-  return (a.n_feat + fpw - 1) / fpw;
-}
-
-hipError_t launch_ffn_down(const FfnGemmArgs& a, bool bf16, hipStream_t stream, bool counters_clear) {
   if (bf16) {
-    if (few_ok(a)) return launch_ffn_few(a, 1, true, stream);
-    const MidPlan mp = mid_of(a, 1);
-    if (mp.use) return launch_ffn_mid(a, 1, mp, stream);
-    int n_tt, n_ft;
-    const GemmSplit sp = pp2_plan<1>(a, &n_tt, &n_ft);
-    if (down_on_pp2(a, sp, n_tt, n_ft)) return launch_pp2<1, 8, true>(a, sp, n_tt, n_ft, stream, counters_clear);
     if (a.n_feat < 3072) return launch_cfg<true, 1, 256, 128, 4, 2, 2, 1, 64>(a, stream);
     return launch_cfg<true, 1, 128, 128, 2, 2, 2, 1, 64>(a, stream);
   }
-  if (few32_ok(a, 1)) return launch_ffn_few(a, 1, false, stream);
   if (grid_tiles(a, 128, 128) < 128) return launch_cfg<false, 1, 32, 32, 1, 1, 2>(a, stream);
   return launch_cfg<false, 1, 128, 128, 2, 2, 2>(a, stream);
 }

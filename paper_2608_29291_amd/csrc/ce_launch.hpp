@@ -88,27 +88,44 @@ struct FfnGemmArgs {
   BypassCopy copy;
 };
 
+// The kernel that a gate/up (mode 0) or down (mode 1) launch takes, decided once
+// per launch from its arguments (with row_flag: the pruned FFN's down).
+enum FfnKernel {
+  kFfnTiles = 0,  // ffn_gemm_kernel
+  kFfnWide = 1,   // ffn_gemm_pp2_kernel, the 256 x 256 tiles
+  kFfnFew = 2,    // ce_ffn_few.hip
+  kFfnMid = 3,    // ce_ffn_mid.hip
+};
+struct FfnRoute {
+  FfnKernel kernel;
+  MidPlan mid;      // kFfnMid
+  GemmSplit split;  // kFfnWide
+  int n_tt, n_ft;   // kFfnWide: token and feature tiles
+};
+FfnRoute ffn_route(const FfnGemmArgs& a, int mode, bool bf16);
+
 // counters_clear: this launch's arrival counters (tile_cnt) were already
 // cleared on this stream (by the previous kernel through clear_cnt); else a
 // fill kernel clears them first when the launch splits.
-hipError_t launch_ffn_gateup(const FfnGemmArgs& a, bool bf16, hipStream_t stream, bool counters_clear = false);
-hipError_t launch_ffn_down(const FfnGemmArgs& a, bool bf16, hipStream_t stream, bool counters_clear = false);
+hipError_t launch_ffn_gateup(const FfnGemmArgs& a, const FfnRoute& r, bool bf16, hipStream_t stream,
+                             bool counters_clear = false);
+hipError_t launch_ffn_down(const FfnGemmArgs& a, const FfnRoute& r, bool bf16, hipStream_t stream,
+                           bool counters_clear = false);
 // Whether the gate/up launch takes the bypass copy: when it is not the 256 x
 // 256 kernel, that is on small batches, where a launch of its own is mostly
 // start-up (2.4 to 5 us of 61 to 95 us per block). Behind the 256 x 256 tiles,
 // on the CUs of their last round, the copy held up the tiles there (370 -> 375
 // us per block at the Show-o2 understanding shape).
-bool gateup_takes_copy(const FfnGemmArgs& gateup, bool bf16);
-// Number of arrival counters a GEMM launch with these arguments uses (0: no
-// split); mode 0 = gate/up, 1 = down.
-int ffn_split_counters(const FfnGemmArgs& a, int mode, bool bf16);
-// Down GEMM of the pruned FFN, with the same choice of kernel; the caller
-// checks ffn_pruned_ok first.
-hipError_t launch_ffn_down_pruned(const FfnGemmArgs& a, hipStream_t stream, bool counters_clear);
+inline bool gateup_takes_copy(const FfnRoute& gateup) { return gateup.kernel != kFfnWide; }
+// Number of arrival counters a launch uses (0: no split).
+inline int ffn_split_counters(const FfnRoute& r) {
+  return r.kernel == kFfnWide && r.split.pieces > 1 ? kXcdCount * r.split.tail_x : 0;
+}
 bool ffn_pruned_ok(const FfnGemmArgs& gateup, const FfnGemmArgs& down);
 
-// FFN GEMMs for at most kFewRows packed rows (bf16, see ce_ffn_few.hip); mode
-// 0 = gate/up, 1 = down. No split counters, no pruning.
+// FFN GEMMs with few rows to a workgroup's features (ce_ffn_few.hip): bf16, at
+// most kFewRows packed rows, or fp32 in row tiles (up to 1024 rows for down);
+// mode 0 = gate/up, 1 = down, also the pruned FFN's. No split counters.
 constexpr int kFewGapFeatures = 16;  // features per layer-gap slot of its down kernel
 hipError_t launch_ffn_few(const FfnGemmArgs& a, int mode, bool bf16, hipStream_t stream);
 
@@ -133,9 +150,9 @@ hipError_t launch_saliency_segments(const FfnGemmArgs& gateup, const int32_t* ke
                                     int B, int n_keep, float delta, float* chunk_tot, float* saliency, float* lambda,
                                     uint8_t* use_pruned, uint8_t* row_flag, int32_t* seq_cnt, hipStream_t stream);
 
-// Gap partial-sum slots per row (gap_np) of the down kernel that
-// launch_ffn_down picks for these arguments: ceil(d / features per wave).
-int ffn_down_gap_slots(const FfnGemmArgs& a, bool bf16);
+// Gap partial-sum slots per row (gap_np) of a down launch: ceil(d / features
+// per slot).
+int ffn_down_gap_slots(const FfnGemmArgs& a, const FfnRoute& r, bool bf16);
 
 struct ScoreArgs {
   const char* hidden;

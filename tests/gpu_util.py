@@ -83,6 +83,20 @@ def rel_err(gpu, ref):
     return float(np.max(np.abs(gpu - ref))) / max(float(np.max(np.abs(ref))), 1e-30)
 
 
+# kernels of the FFN launches (enum FfnKernel in csrc/ce_launch.hpp)
+TILES, WIDE, FEW, MID = range(4)
+
+
+def ffn_route(mode, cap, d, F, n_sets=1, dtype="bf16", pruned=False):
+    """(kernel, weight blocks, token blocks, pieces over K, absorb) of a gate/up
+    (mode 0) or down (mode 1) launch over `cap` packed rows (host query)."""
+    import ctypes
+    out = (ctypes.c_int32 * 5)()
+    code = ce.CE_BF16 if dtype == "bf16" else ce.CE_F32
+    assert ce.lib.ce_ffn_route(mode, cap, d, F, n_sets, code, int(pruned), out) == ce.CE_OK
+    return tuple(out)
+
+
 LOGIT_TOL = {"f32": 1e-5, "bf16": 1e-4}
 OUT_TOL = {"f32": 1e-5, "bf16": 2e-2}
 # The FFN term of a retained row, Y - H, against the oracle's FFN(H), element

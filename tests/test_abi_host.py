@@ -250,6 +250,27 @@ int main(void) {
     assert r.returncode == 0 and r.stdout.startswith("OK"), r.stdout + r.stderr
 
 
+def ffn_route(mode, cap, d, F, sets=1, dtype=ce.CE_BF16, pruned=0):
+    out = (ctypes.c_int32 * 5)()
+    r = ce.lib.ce_ffn_route(mode, cap, d, F, sets, dtype, pruned, out)
+    return r if r < 0 else tuple(out)
+
+
+def test_ffn_route_query():
+    """The host query of the kernel that an FFN launch takes (kernel, weight and
+    token blocks, pieces, absorb): 0 tiles, 1 the 256 x 256 kernel, 2 few rows, 3
+    mid-size counts."""
+    assert ffn_route(0, 16, 3584, 18944) == (2, 0, 0, 1, 0) == ffn_route(1, 64, 1536, 8960)
+    assert ffn_route(0, 402, 1536, 8960) == (3, 4, 5, 1, 0) and ffn_route(1, 402, 1536, 8960)[:3] == (3, 2, 5)
+    assert ffn_route(0, 4408, 1536, 8960) == (1, 0, 0, 1, 1) and ffn_route(1, 4408, 1536, 8960) == (1, 0, 0, 2, 0)
+    assert ffn_route(0, 4408, 1536, 8960, pruned=1)[4] == 0  # its segment sums take tiles of 256 rows
+    assert ffn_route(1, 3600, 3584, 18944)[0] == 1 and ffn_route(1, 2400, 3584, 18944)[0] == 0
+    assert ffn_route(1, 2400, 3584, 18944, pruned=1)[0] == 1
+    assert ffn_route(1, 160, 256, 1024, dtype=ce.CE_F32)[0] == 2 and ffn_route(1, 4000, 256, 1024, dtype=ce.CE_F32)[0] == 0
+    for bad in ((2, 16, 256, 512), (0, 0, 256, 512), (0, 16, 256, 512, 3), (0, 16, 256, 512, 1, 7)):
+        assert ffn_route(*bad) == ce.CE_ERR_INVALID_ARG
+
+
 def test_drop_stability_validation():
     b = _batch()
     st = lambda bb, tpt=FAKE, tpr=FAKE, jac=FAKE: ce.lib.ce_drop_stability(
