@@ -96,12 +96,19 @@ void gemm_items(int mode, int cap, int d, int d_ff, int n_sets, int elem, int64_
   *ns = (int)(k_bytes / 128);
 }
 
-// Both kernels' times in microseconds, fitted to launches of 65 to 4408 rows at
-// d, d_ff = 1536, 8960 and 3584, 18944 (within about 15%); only their order
-// matters. The mid-size kernel: rounds of 256 workgroups x stages (128 bytes
-// of K) x the stage time of its tile, or the weights' time from memory; down
-// adds the pieces' sums. The 256 x 256 kernel: gate/up by rounds; down, which
-// splits its tiles over K, with what its last-arriving workgroups add.
+// Both kernels' times in microseconds; only their order matters. The tile and
+// the pieces come from the mid-size kernel's time: rounds of 256 workgroups x
+// stages (128 bytes of K) x the stage time of its tile, or the weights' time
+// from memory; down adds the pieces' sums. Gate/up is compared with the rounds
+// of the 256 x 256 kernel, by a clear margin: both come in rounds, and where the
+// other's are nearly empty (d 1536: 800 to 1100 rows, d 2048: 620 to 800) this
+// one is 1.1 to 1.3 times as fast, between them 0.8 to 1 times. Down is compared
+// with the split 256 x 256 kernel by a second fit of both, each with a standard
+// deviation of 6% over 65 to 4640 rows at d, d_ff = 1024, 4096; 1536, 8960; 2048,
+// 11008; 2560, 10240; 3584, 18944: of 212 measured sizes it takes one where it
+// is slower by 2%, and leaves four where it would be faster by up to 7%. It is
+// taken up to 2688 rows at d 1536, 2048 at 2048, 1536 at 2560, 768 at 3584 (less
+// with two weight sets) and at every count at 1024.
 MidPlan mid_plan(int mode, int cap, int n_feat, int n_sets, int ns) {
   constexpr int kM[] = {2, 3, 4, 5, 6, 8};
   constexpr double kT2[] = {0.35, 0.45, 0.58, 0.72, 0.80, 1.05};  // 128 weight rows
@@ -141,11 +148,20 @@ MidPlan mid_plan(int mode, int cap, int n_feat, int n_sets, int ns) {
   } else {
     const int64_t items = (int64_t)((cap + 255) / 256 + n_sets - 1) * ((n_feat + 255) / 256);
     const GemmSplit sp = gemm_split(items, ns);
-    const int full = sp.whole_x / kCusPerXcd;  // full rounds before the split ones
-    // (two pieces: the last adds one other partial tile to its own sums)
-    big = sp.pieces > 1 ? (sp.pieces == 2 ? 20.0 : 38.0) + 1.3 * (full * ns + (double)ns / sp.pieces) +
-                              0.28 * (double)items
-                        : 8.0 + 1.3 * ns * (double)((items + kCus - 1) / kCus);
+    if (sp.pieces > 1) {
+      constexpr double kT[] = {0.375, 0.485, 0.585, 0.655, 0.735, 0.0, 0.915};  // stage time by m, from 2
+      const double t = kT[best.m - 2];
+      const double work = (double)((cap + 32 * best.m - 1) / (32 * best.m) + n_sets - 1) * ((n_feat + 127) / 128) *
+                          best.pieces / kCus;  // rounds, the last one's fill as a fraction
+      const double rounds = ceil(work);
+      const double loop = 8.2 + rounds * ns / best.pieces * t * (0.825 + 0.175 * work / rounds);
+      const double mid = (loop < mem ? mem : loop) + 3.8 + (double)best.pieces * cap * n_feat * 4.0 / 3.8e6;
+      const double wide = 40.0 + ns / 256.0 * (1.30 * (double)items + 0.157 * cap * (double)n_feat / 65536.0) +
+                          1.36 * sp.pieces;
+      best.use = mid < 0.99 * wide;
+      return best;
+    }
+    big = 8.0 + 1.3 * ns * (double)((items + kCus - 1) / kCus);
   }
   best.use = best_c < 0.88 * big;  // clearly, the fit being what it is
   return best;

@@ -271,6 +271,16 @@ def test_ffn_route_query():
         assert ffn_route(*bad) == ce.CE_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("d,F,last", [(1024, 4096, None), (1536, 8960, 2688), (2048, 11008, 2048), (2560, 10240, 1536),
+                                      (3584, 18944, 768), (4096, 14336, 1024)])
+def test_down_leaves_the_mid_size_kernel_once(d, F, last):
+    """Down's choice is one line in the packed count, between the sizes where the
+    mid-size kernel measured faster and slower than the split 256 x 256 tiles (one
+    weight set; d 4096 was measured and not fitted)."""
+    taken = [n for n in range(65, 4700) if ffn_route(1, n, d, F)[0] == 3]
+    assert taken == list(range(65, (last or 4699) + 1))
+
+
 def test_drop_stability_validation():
     b = _batch()
     st = lambda bb, tpt=FAKE, tpr=FAKE, jac=FAKE: ce.lib.ce_drop_stability(
