@@ -1,0 +1,179 @@
+"""The FFN GEMMs on every kernel and tile that the dispatch reaches, in the fused
+block with its layer gap and in the pruned FFN, against float64 on the GPU. Each
+case states the kernels it is for and asserts that the dispatch takes them, so a
+change of the rules cannot empty it.
+
+Bars, per element. Products of bf16 inputs are exact in fp32 and summed over K
+values: sum |a w| sqrt(K) 2^-24, and 2^-8 of the result for its rounding to
+bf16. The activation's errors pass through SwiGLU with its derivatives (|silu'|
+<= 1.1) and through the down product with its weights' magnitudes; the output
+adds one rounding. The layer gap's bars as in test_gpu_layer_gap.py.
+"""
+import pytest
+
+TILES, WIDE, FEW, MID = range(4)
+N_KEEP = 0.75  # share of the channels that the pruned FFN keeps
+
+# (d, d_ff, packed rows, weight sets): (gate/up kernel, down kernel)
+CASES = {
+    # mid-size kernel: its token tiles of 64 to 256 rows with 128 and 256 weight
+    # rows, at the counts where one tile hands over to the next (multiples of its
+    # rows, and one more)
+    **{(1024, 4096, n, s): (MID, MID) for n in (65, 96, 256, 257, 384, 385, 512, 513, 640, 641, 768, 769, 1024, 1025)
+       for s in (1, 2) if (n, s) not in ((1024, 2),)},
+    (576, 1088, 3600, 1): (MID, MID), (576, 1088, 3500, 2): (MID, MID),
+    (1024, 4096, 3400, 1): (WIDE, MID), (1536, 2304, 1441, 2): (MID, MID),
+    (1536, 8960, 97, 1): (MID, MID), (1536, 8960, 193, 1): (MID, MID), (1536, 8960, 289, 1): (MID, MID),
+    (1536, 8960, 402, 1): (MID, MID), (1536, 8960, 673, 1): (WIDE, MID), (1536, 8960, 864, 2): (MID, MID),
+    (1536, 8960, 2400, 1): (WIDE, MID), (1536, 8960, 2688, 1): (WIDE, MID),
+    # 256 x 256 kernel: absorbed last tiles (1 and 32 rows), split gate/up (2 to 5
+    # pieces), split down (2 to 11), whole tiles
+    (1536, 8960, 513, 1): (WIDE, MID), (1536, 8960, 544, 1): (WIDE, MID), (1536, 8960, 545, 1): (WIDE, MID),
+    (1536, 8960, 2689, 1): (WIDE, WIDE), (1536, 8960, 3329, 1): (WIDE, WIDE), (1536, 8960, 3300, 2): (WIDE, WIDE),
+    (1024, 4096, 2600, 1): (WIDE, MID), (2048, 11008, 1400, 1): (WIDE, MID), (2048, 11008, 2100, 1): (WIDE, WIDE),
+    (3584, 18944, 490, 1): (WIDE, MID), (3584, 18944, 800, 1): (WIDE, WIDE), (3584, 18944, 500, 2): (WIDE, WIDE),
+    (3584, 18944, 3600, 1): (WIDE, WIDE), (3584, 18944, 4615, 1): (WIDE, WIDE),
+    # down on the smaller tiles where few 256 x 256 ones cannot split
+    (2048, 11008, 4200, 1): (WIDE, TILES), (3584, 18944, 2400, 1): (WIDE, TILES),
+    # few-row kernel, one row block to four, and past it
+    (1024, 4096, 16, 1): (FEW, FEW), (1024, 4096, 17, 2): (FEW, FEW), (1024, 4096, 33, 1): (FEW, FEW),
+    (1024, 4096, 64, 2): (FEW, FEW),
+}
+
+
+def test_cases_take_the_kernels_they_name():
+    """And together every tile of the mid-size kernel and every kind of split."""
+    G = pytest.importorskip("gpu_util")
+    seen = [set(), set()]
+    for (d, F, n, s), kernels in CASES.items():
+        for mode in (0, 1):
+            r = G.ffn_route(mode, n, d, F, s)
+            assert r[0] == kernels[mode], (d, F, n, s, mode, r)
+            seen[mode].add(r[:3] if r[0] == MID else (r[0], min(r[3], 5), r[4]))
+    assert {x[1:] for x in seen[0] if x[0] == MID} == {(2, m) for m in (2, 3, 4, 5, 6, 8)} | {(4, m) for m in (3, 4, 5)}
+    assert {x[1:] for x in seen[1] if x[0] == MID} == {(2, m) for m in (2, 3, 4, 5, 6, 8)}
+    assert {x for x in seen[0] if x[0] == WIDE} >= {(WIDE, 1, 1), (WIDE, 2, 0), (WIDE, 4, 0), (WIDE, 5, 0)}
+    assert {x for x in seen[1] if x[0] == WIDE} >= {(WIDE, p, 0) for p in (1, 2, 3, 4, 5)}
+
+
+def ffn64(torch, x, wg, wu, wd):
+    """float64 SwiGLU of bf16 rows, with the bound on |z_gpu - z|."""
+    g, u = x.double() @ wg.double().T, x.double() @ wu.double().T
+    e = x.shape[1] ** 0.5 * 2.0 ** -24
+    eg, eu = (e * (x.abs().float() @ w.abs().float().T).double() for w in (wg, wu))
+    s = g * torch.sigmoid(g)
+    z = s * u
+    return z, 1.1 * u.abs() * eg + s.abs() * eu + (2.0 ** -8 + 2.0 ** -20) * z.abs()
+
+
+def down64(torch, z, ez, wd):
+    """float64 down product, with the bound on the GPU's before its rounding."""
+    w = wd.double()
+    y = z @ w.T
+    return y, (ez + z.shape[1] ** 0.5 * 2.0 ** -24 * z.abs()) @ w.abs().T
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,F,n,sets", list(CASES))
+def test_block_gap_and_pruned(d, F, n, sets):
+    import torch
+
+    import gpu_util as G
+    import paper_2608_29291_amd as ce
+    g = torch.Generator("cuda").manual_seed(n + sets)
+    bf, f32 = torch.bfloat16, torch.float32
+
+    def rnd(*shape):
+        return torch.randn(shape, generator=g, device="cuda")
+
+    # two sequences: kept tokens and 8 routable ones each, of which half stay
+    B, extra = 2, 8
+    lens = [n // 3, n - n // 3]
+    flags, offs = [], [0]
+    for k in lens:
+        f = torch.full((k - extra // 2 + extra,), ce.CE_TOK_KEEP, dtype=torch.uint8)
+        f[torch.randperm(len(f), generator=torch.Generator().manual_seed(k))[:extra]] = 0
+        if sets == 2:
+            f[1::3] |= ce.CE_TOK_GEN
+        flags.append(f)
+        offs.append(offs[-1] + len(f))
+    flags = torch.cat(flags).cuda()
+    T = offs[-1]
+    batch = ce.Batch(torch.tensor(offs, dtype=torch.int32).cuda(), flags, torch.full((B,), 0.5, device="cuda"), 0.5, n)
+    sc = ce.Scorer(rnd(32, d).to(bf), rnd(32), rnd(4, 32, d).to(bf), rnd(4, 32))
+    W = [((rnd(F, d) * d ** -0.5).to(bf), (rnd(F, d) * d ** -0.5).to(bf), (rnd(d, F) * F ** -0.5).to(bf))
+         for _ in range(sets)]
+    ffn = ce.FFN(*[list(x) for x in zip(*W)])
+    h = rnd(T, d).to(bf)
+    out = torch.full_like(h, 3.0)
+    ki, ko = torch.full((n,), -7, dtype=torch.int32, device="cuda"), torch.empty(B + 1, dtype=torch.int32, device="cuda")
+    cos, (ra, rr, gap) = torch.empty(T, device="cuda"), (torch.empty(B, device="cuda") for _ in range(3))
+    ws = ce.alloc_workspace(ce.CE_WS_BLOCK_GAP, batch, d, F, ce.CE_BF16)
+    ce.ce_routed_block_gap(batch, h, out, sc, ffn, ws, 0.004, cos, ra, rr, gap, kept_idx_out=ki, kept_offsets_out=ko)
+    plain = h.clone()
+    ce.ce_routed_block(batch, plain, plain, sc, ffn, ce.alloc_workspace(ce.CE_WS_BLOCK, batch, d, F, ce.CE_BF16))
+    torch.cuda.synchronize()
+    assert ko.tolist() == [0, lens[0], n]
+    kept = ki.long()
+    dropped = torch.ones(T, dtype=torch.bool, device="cuda")
+    dropped[kept] = False
+    assert torch.equal(out[dropped], h[dropped]) and torch.equal(out, plain)
+
+    # the pruned FFN on the packed rows: no sequence pruned, then all
+    rows = h[kept].contiguous()
+    norms = torch.empty(sets * F, device="cuda")
+    ce.ce_ffn_down_colnorms(ffn, norms)
+    n_keep = int(N_KEEP * F) // 64 * 64
+    sal, lam = torch.empty((B, F), device="cuda"), torch.empty(B, device="cuda")
+    use = torch.empty(B, dtype=torch.uint8, device="cuda")
+    wsp = ce.alloc_workspace(ce.CE_WS_FFN_PRUNED, batch, d, F, ce.CE_BF16)
+    full, cut = (torch.full_like(rows, float("nan")) for _ in range(2))
+    for delta, y in ((-1.0, full), (1.0, cut)):
+        ce.ce_routed_ffn_pruned(batch, rows, ki, ko, ffn, norms, n_keep, delta, y, sal, lam, use, wsp)
+        torch.cuda.synchronize()
+        assert use.tolist() == [int(delta > 0)] * B
+
+    sets_of = (flags[kept] & ce.CE_TOK_GEN != 0).long() if sets == 2 else torch.zeros(n, dtype=torch.long, device="cuda")
+    sal64, esal = torch.zeros((B, F), dtype=torch.float64, device="cuda"), torch.zeros((B, F), dtype=torch.float64, device="cuda")
+    worst = 0.0
+    for s in range(sets):
+        mine = (sets_of == s).nonzero()[:, 0]
+        for at in mine.split(512):
+            z, ez = ffn64(torch, rows[at], *W[s])
+            for y, k in ((full, F), (cut, n_keep)):
+                ref, err = down64(torch, z[:, :k], ez[:, :k], W[s][2][:, :k])
+                over = (y[at].double() - ref).abs() / (err + 2.0 ** -8 * ref.abs())
+                assert over.max() <= 1, (k, over.max())
+            ref, err = down64(torch, z, ez, W[s][2])
+            ref += rows[at].double()
+            over = (out[kept[at]].double() - ref).abs() / (err + 2.0 ** -8 * ref.abs())
+            worst = max(worst, float(over.max()))
+            nm = norms[s * F:(s + 1) * F].double()
+            for b in range(B):
+                m = (at >= int(ko[b])) & (at < int(ko[b + 1]))
+                sal64[b] += z[m].abs().sum(0) * nm / lens[b]
+                esal[b] += ez[m].sum(0) * nm / lens[b]
+    print(f"[ffn {d}/{F} n={n} sets={sets}] {[G.ffn_route(m, n, d, F, sets)[:4] for m in (0, 1)]} block {worst:.2f} of the bar",
+          flush=True)
+    assert worst <= 1
+    assert ((sal.double() - sal64).abs() <= esal + 2.0 ** -16 * sal64).all()
+    # the layer gap's cosines, of the states as stored
+    x, y = h.double(), out.double()
+    c = (x * y).sum(1) / (x.norm(dim=1) * y.norm(dim=1))
+    assert (cos.double() - c).abs().max() <= 1e-7
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1024, 1025])
+def test_fp32_handover(n):
+    """fp32 down: the K-split kernel up to 1024 rows, 32 x 32 tiles past it."""
+    import gpu_util as G
+    from ce_workloads import TOK_KEEP, make_workload
+    assert [G.ffn_route(1, n, 256, 512, dtype="f32")[0], G.ffn_route(0, n, 256, 512, dtype="f32")[0]] == \
+        [FEW if n <= 1024 else TILES, FEW]
+    wl = make_workload("few32", [[(8, 0), (n - 4, TOK_KEEP)]], d=256, F=512, r_c=32, r_e=32, keep=0.5, dtype="f32",
+                       seed=n, biases=True)
+    r = G.run_block(wl)
+    assert int(r["koff"][-1]) == n
+    err, _ = G.check_block(wl, r)
+    print(f"[fp32 n={n}] rel err {err:.2e}", flush=True)
