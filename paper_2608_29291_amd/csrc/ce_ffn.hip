@@ -1293,7 +1293,7 @@ inline bool few_ok(const FfnGemmArgs& a) {
 // rows 326 and 319; down 128 rows 56 and 201, 512 rows 206 and 223.
 inline bool few32_ok(const FfnGemmArgs& a, int mode) {
   if (!big_ok(a)) return false;
-  return mode == 0 ? a.cap <= 256 || grid_tiles(a, 64, 128) < 128 : a.cap <= 1024 && grid_tiles(a, 128, 128) < 128;
+  return mode == 0 ? a.cap <= 256 || grid_tiles(a, 64, 128) < 128 : a.cap <= kFewRows32Down && grid_tiles(a, 128, 128) < 128;
 }
 
 // The mid-size kernel's plan (use == 0: not taken).

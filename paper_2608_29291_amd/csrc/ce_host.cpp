@@ -287,9 +287,11 @@ WsLayout ws_layout(int which, int B, int T, int cap, int d, int d_ff, int elem) 
     L.seq_cnt = take(sB * 4);
   }
   if (which == CE_WS_BLOCK_GAP) {
-    // slots of the down GEMM per row; each covers >= 16 features
+    // slots of the down GEMM per row: of 16 features on the few-row kernel, of at
+    // least 64 (bf16) or 32 on the others (ffn_down_gap_slots)
     const size_t sD = (size_t)(d < 0 ? 0 : d);
-    L.gap_part = take(sC * ((sD + 15) / 16) * 4 * sizeof(double));
+    const size_t f = cap <= (elem == 2 ? kFewRows : kFewRows32Down) ? 16 : elem == 2 ? 64 : 32;
+    L.gap_part = take(sC * ((sD + f - 1) / f) * 4 * sizeof(double));
   }
   L.total = off;
   return L;

@@ -27,10 +27,11 @@ struct WsLayout {
   size_t grp_rows;   // int32 [cap]    (MoT grouping)
   size_t grp_n0;     // int32          (MoT group size)
   size_t act;        // dtype [cap * d_ff] SwiGLU activations
-  size_t gemm_part;  // float [slots x 256 x 256] K-piece partial sums of the FFN GEMMs' tail tiles
+  size_t gemm_part;  // float [slots x 256 x 256] K-piece partial sums of the FFN GEMMs' tail tiles, or
+                     // [pieces x cap x d] of the mid-size down kernel (the larger)
   size_t gu_cnt;     // int32 [kSplitMaxSlots] arrival counters of the gate/up tail tiles
   size_t dn_cnt;     // int32 [kSplitMaxSlots] arrival counters of the down tail tiles
-  size_t gap_part;   // double [cap x ceil(d / 16) x 4] layer-gap partial sums (CE_WS_BLOCK_GAP)
+  size_t gap_part;   // double [cap x slots x 4] layer-gap partial sums (CE_WS_BLOCK_GAP)
   size_t row_seq;    // int32 [cap] sequence of each packed row (CE_WS_FFN_PRUNED)
   size_t sal_seg;    // float [tiles x kSalSegs x d_ff] per-segment |z| sums (CE_WS_FFN_PRUNED)
   size_t sal_meta;   // int32 [tiles x (kSalSegs + 1)] segment counts and sequences (CE_WS_FFN_PRUNED)
@@ -100,8 +101,10 @@ struct MidPlan {
   int pieces;
 };
 constexpr int kMidMaxPieces = 32;
-// At most this many packed rows run on the few-row kernel (ce_ffn_few.hip).
+// At most this many packed rows run on the few-row kernel (ce_ffn_few.hip):
+// bf16, and fp32 down.
 constexpr int kFewRows = 64;
+constexpr int kFewRows32Down = 1024;
 MidPlan mid_plan(int mode, int cap, int n_feat, int n_sets, int ns);
 
 // The one-workgroup-per-sequence signal kernels use workgroups of 1024 threads

@@ -214,6 +214,16 @@ def test_workspace_sizes_grow_with_capacity():
     assert ce.lib.ce_workspace_size(ce.CE_WS_BLOCK, ctypes.byref(small), 256, 512, 3) == 0
 
 
+@pytest.mark.parametrize("dtype,cap,width", [(ce.CE_BF16, 64, 16), (ce.CE_BF16, 65, 64), (ce.CE_BF16, 8704, 64),
+                                             (ce.CE_F32, 1024, 16), (ce.CE_F32, 1025, 32)])
+def test_gap_workspace_holds_the_slots_in_use(dtype, cap, width):
+    """Three sums (of four doubles) per row and `width` features."""
+    b = _batch(T=cap, cap=cap)
+    d, F = 1536, 8960
+    size = lambda which: ce.lib.ce_workspace_size(which, ctypes.byref(b), d, F, dtype)
+    assert 0 <= size(ce.CE_WS_BLOCK_GAP) - size(ce.CE_WS_BLOCK) - cap * d // width * 32 < 256
+
+
 def test_host_logic_under_sanitizers(tmp_path):
     """Host-only build of the validation / keep-count code with ASan + UBSan (g++, no HIP)."""
     src = os.path.join(ROOT, "paper_2608_29291_amd", "csrc", "ce_host.cpp")

@@ -73,9 +73,15 @@ def down64(torch, z, ez, wd):
     return y, (ez + z.shape[1] ** 0.5 * 2.0 ** -24 * z.abs()) @ w.abs().T
 
 
+# two sequences each, and a few with so many that a token tile holds more of them
+# than its segment sums (9 rows each, and 60)
+BATCHES = [(*c, 2) for c in CASES] + [(1536, 8960, 2700, 1, 300), (1536, 8960, 3420, 1, 57), (1536, 8960, 3420, 2, 57),
+                                      (1024, 4096, 900, 1, 100), (1024, 4096, 48, 1, 24)]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("d,F,n,sets", list(CASES))
-def test_block_gap_and_pruned(d, F, n, sets):
+@pytest.mark.parametrize("d,F,n,sets,B", BATCHES)
+def test_block_gap_and_pruned(d, F, n, sets, B):
     import torch
 
     import gpu_util as G
@@ -86,9 +92,9 @@ def test_block_gap_and_pruned(d, F, n, sets):
     def rnd(*shape):
         return torch.randn(shape, generator=g, device="cuda")
 
-    # two sequences: kept tokens and 8 routable ones each, of which half stay
-    B, extra = 2, 8
-    lens = [n // 3, n - n // 3]
+    # kept tokens and a few routable ones in each sequence, of which half stay
+    lens = [n // 3, n - n // 3] if B == 2 else [n // B] * B
+    extra = min(8, 2 * min(lens))
     flags, offs = [], [0]
     for k in lens:
         f = torch.full((k - extra // 2 + extra,), ce.CE_TOK_KEEP, dtype=torch.uint8)
@@ -113,13 +119,13 @@ def test_block_gap_and_pruned(d, F, n, sets):
     plain = h.clone()
     ce.ce_routed_block(batch, plain, plain, sc, ffn, ce.alloc_workspace(ce.CE_WS_BLOCK, batch, d, F, ce.CE_BF16))
     torch.cuda.synchronize()
-    assert ko.tolist() == [0, lens[0], n]
+    assert ko.tolist() == [sum(lens[:b]) for b in range(B + 1)]
     kept = ki.long()
     dropped = torch.ones(T, dtype=torch.bool, device="cuda")
     dropped[kept] = False
     assert torch.equal(out[dropped], h[dropped]) and torch.equal(out, plain)
 
-    # the pruned FFN on the packed rows: no sequence pruned, then all
+    # the pruned FFN on the packed rows: no sequence pruned, all, and half of them
     rows = h[kept].contiguous()
     norms = torch.empty(sets * F, device="cuda")
     ce.ce_ffn_down_colnorms(ffn, norms)
@@ -127,11 +133,14 @@ def test_block_gap_and_pruned(d, F, n, sets):
     sal, lam = torch.empty((B, F), device="cuda"), torch.empty(B, device="cuda")
     use = torch.empty(B, dtype=torch.uint8, device="cuda")
     wsp = ce.alloc_workspace(ce.CE_WS_FFN_PRUNED, batch, d, F, ce.CE_BF16)
-    full, cut = (torch.full_like(rows, float("nan")) for _ in range(2))
-    for delta, y in ((-1.0, full), (1.0, cut)):
+    full, cut, some = (torch.full_like(rows, float("nan")) for _ in range(3))
+    for delta, y in ((-1.0, full), (1.0, cut), (None, some)):
+        delta = float(lam.mean()) if delta is None else delta
         ce.ce_routed_ffn_pruned(batch, rows, ki, ko, ffn, norms, n_keep, delta, y, sal, lam, use, wsp)
         torch.cuda.synchronize()
-        assert use.tolist() == [int(delta > 0)] * B
+        assert torch.equal(use.bool(), lam <= delta)
+    assert 0 < int(use.sum()) < B
+    seq = torch.repeat_interleave(torch.arange(B, device="cuda"), torch.tensor(lens, device="cuda"))
 
     sets_of = (flags[kept] & ce.CE_TOK_GEN != 0).long() if sets == 2 else torch.zeros(n, dtype=torch.long, device="cuda")
     sal64, esal = torch.zeros((B, F), dtype=torch.float64, device="cuda"), torch.zeros((B, F), dtype=torch.float64, device="cuda")
@@ -140,20 +149,21 @@ def test_block_gap_and_pruned(d, F, n, sets):
         mine = (sets_of == s).nonzero()[:, 0]
         for at in mine.split(512):
             z, ez = ffn64(torch, rows[at], *W[s])
-            for y, k in ((full, F), (cut, n_keep)):
+            cuts = use[seq[at]].bool()
+            for y, k, m in ((full, F, None), (cut, n_keep, None), (some, F, ~cuts), (some, n_keep, cuts)):
                 ref, err = down64(torch, z[:, :k], ez[:, :k], W[s][2][:, :k])
                 over = (y[at].double() - ref).abs() / (err + 2.0 ** -8 * ref.abs())
-                assert over.max() <= 1, (k, over.max())
+                over = over if m is None else over[m]
+                assert over.numel() == 0 or over.max() <= 1, (k, over.max())
             ref, err = down64(torch, z, ez, W[s][2])
             ref += rows[at].double()
             over = (out[kept[at]].double() - ref).abs() / (err + 2.0 ** -8 * ref.abs())
             worst = max(worst, float(over.max()))
             nm = norms[s * F:(s + 1) * F].double()
-            for b in range(B):
-                m = (at >= int(ko[b])) & (at < int(ko[b + 1]))
-                sal64[b] += z[m].abs().sum(0) * nm / lens[b]
-                esal[b] += ez[m].sum(0) * nm / lens[b]
-    print(f"[ffn {d}/{F} n={n} sets={sets}] {[G.ffn_route(m, n, d, F, sets)[:4] for m in (0, 1)]} block {worst:.2f} of the bar",
+            share = nm / torch.tensor(lens, device="cuda")[seq[at], None]
+            sal64.index_add_(0, seq[at], z.abs() * share)
+            esal.index_add_(0, seq[at], ez * share)
+    print(f"[ffn {d}/{F} n={n} sets={sets} B={B}] {[G.ffn_route(m, n, d, F, sets)[:4] for m in (0, 1)]} block {worst:.2f} of the bar",
           flush=True)
     assert worst <= 1
     assert ((sal.double() - sal64).abs() <= esal + 2.0 ** -16 * sal64).all()
@@ -166,8 +176,14 @@ def test_block_gap_and_pruned(d, F, n, sets):
 @pytest.mark.gpu
 @pytest.mark.parametrize("n", [1024, 1025])
 def test_fp32_handover(n):
-    """fp32 down: the K-split kernel up to 1024 rows, 32 x 32 tiles past it."""
+    """fp32 down: the K-split kernel up to 1024 rows, 32 x 32 tiles past it, each
+    with its own slots of the layer gap's sums."""
+    import numpy as np
+    import torch
+
     import gpu_util as G
+    import paper_2608_29291_amd as ce
+    from oracle import layer_gap
     from ce_workloads import TOK_KEEP, make_workload
     assert [G.ffn_route(1, n, 256, 512, dtype="f32")[0], G.ffn_route(0, n, 256, 512, dtype="f32")[0]] == \
         [FEW if n <= 1024 else TILES, FEW]
@@ -177,3 +193,16 @@ def test_fp32_handover(n):
     assert int(r["koff"][-1]) == n
     err, _ = G.check_block(wl, r)
     print(f"[fp32 n={n}] rel err {err:.2e}", flush=True)
+    dw = G.DevWorkload(wl)
+    T, B = wl.T, wl.B
+    cos, ra, rr, gap = (torch.empty(k, device="cuda") for k in (T, B, B, B))
+    out, (ki, ko) = torch.empty_like(dw.hidden), dw.new_idx()
+    ce.ce_routed_block_gap(dw.batch, dw.hidden, out, dw.scorer, dw.ffn, dw.ws(ce.CE_WS_BLOCK_GAP), 0.004, cos, ra, rr,
+                           gap, kept_idx_out=ki, kept_offsets_out=ko)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(G.host(out), r["y"])
+    pos = np.full(T, -1, np.int32)
+    pos[G.host(ki)] = np.arange(n)
+    _, _, want, c = layer_gap.redundancy_gap(wl.hidden, G.host(out), wl.seq_offsets, pos)
+    np.testing.assert_allclose(G.host(cos), c, rtol=0, atol=1e-7)
+    np.testing.assert_allclose(G.host(gap), want, rtol=0, atol=3e-7)
