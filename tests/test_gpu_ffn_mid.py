@@ -3,7 +3,9 @@ block against the oracle, at the edges of the token tiles and of the pieces
 over K, where the mid-size kernel takes one or both products. Bars as every
 block test: 2e-2 of max |Y|, 1e-2 of max |FFN| beside one rounding of Y; the
 layer gap's as in test_gpu_layer_gap.py. Widths with odd feature tiles (d =
-576: 4.5 tiles of 128, F = 1088: 17 of 64) and enough K for several pieces."""
+576: 4.5 tiles of 128, F = 1088: 17 of 64) and enough K for several pieces.
+These counts reach its tiles of 64 and 96 rows; test_gpu_ffn_routes.py has every
+tile."""
 import numpy as np
 import pytest
 

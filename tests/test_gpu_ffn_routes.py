@@ -87,7 +87,7 @@ def test_block_gap_and_pruned(d, F, n, sets, B):
     import gpu_util as G
     import paper_2608_29291_amd as ce
     g = torch.Generator("cuda").manual_seed(n + sets)
-    bf, f32 = torch.bfloat16, torch.float32
+    bf = torch.bfloat16
 
     def rnd(*shape):
         return torch.randn(shape, generator=g, device="cuda")
@@ -140,6 +140,23 @@ def test_block_gap_and_pruned(d, F, n, sets, B):
         torch.cuda.synchronize()
         assert torch.equal(use.bool(), lam <= delta)
     assert 0 < int(use.sum()) < B
+    # an empty kept prefix, and one of all channels; the staged calls, each of
+    # which clears its own counters, and the whole call twice on one workspace
+    edge, ident = (torch.full_like(rows, float("nan")) for _ in range(2))
+    ce.ce_routed_ffn_pruned(batch, rows, ki, ko, ffn, norms, 0, 1.0, edge, torch.empty_like(sal), torch.empty_like(lam),
+                            torch.empty_like(use), wsp)
+    ce.ce_routed_ffn_pruned(batch, rows, ki, ko, ffn, norms, F, 1.0, ident, torch.empty_like(sal), torch.empty_like(lam),
+                            torch.empty_like(use), wsp)
+    wsf = ce.alloc_workspace(ce.CE_WS_FFN, batch, d, F, ce.CE_BF16)
+    once, again, staged = (torch.full_like(rows, float("nan")) for _ in range(3))
+    act = torch.full((n, F), float("nan"), dtype=bf, device="cuda")
+    ce.ce_routed_ffn(batch, rows, ki, ko, ffn, once, wsf)
+    ce.ce_routed_ffn(batch, rows, ki, ko, ffn, again, wsf)
+    ce.ce_ffn_gateup(batch, rows, ki, ko, ffn, act, wsf)
+    ce.ce_ffn_down(batch, act, ki, ko, ffn, staged, wsf)
+    torch.cuda.synchronize()
+    assert not edge.any() and torch.equal(ident, full)
+    assert torch.equal(once, again) and torch.equal(once, staged)
     seq = torch.repeat_interleave(torch.arange(B, device="cuda"), torch.tensor(lens, device="cuda"))
 
     sets_of = (flags[kept] & ce.CE_TOK_GEN != 0).long() if sets == 2 else torch.zeros(n, dtype=torch.long, device="cuda")
@@ -150,7 +167,7 @@ def test_block_gap_and_pruned(d, F, n, sets, B):
         for at in mine.split(512):
             z, ez = ffn64(torch, rows[at], *W[s])
             cuts = use[seq[at]].bool()
-            for y, k, m in ((full, F, None), (cut, n_keep, None), (some, F, ~cuts), (some, n_keep, cuts)):
+            for y, k, m in ((full, F, None), (once, F, None), (cut, n_keep, None), (some, F, ~cuts), (some, n_keep, cuts)):
                 ref, err = down64(torch, z[:, :k], ez[:, :k], W[s][2][:, :k])
                 over = (y[at].double() - ref).abs() / (err + 2.0 ** -8 * ref.abs())
                 over = over if m is None else over[m]

@@ -53,6 +53,13 @@ def _gateup(G, wl, cap=None):
     return G.host(act)[:T]
 
 
+def _absorbs(G, n, d, F, n_sets=1):
+    """Whether a gate/up launch over n rows runs on the 256 x 256 tiles and
+    absorbs a short last one."""
+    r = G.ffn_route(0, n, d, F, n_sets)
+    return r[0] == G.WIDE and r[4] == 1
+
+
 # (d, d_ff): 3, 4 and 5 superslabs of K (the ext tiles' steady loop runs 1-3
 # times before the two last superslabs); d_ff = 320 leaves a half feature tile
 SHAPES = [(192, 512), (256, 320), (320, 512)]
@@ -72,6 +79,40 @@ def test_gateup_absorbed_rows_bitwise(G, d, F, n, ref_n):
     # a capacity above the packed count sizes the grid for more tiles
     a_cap = _gateup(G, small, cap=ref_n + 64)
     np.testing.assert_array_equal(a_cap, a)
+
+
+# The same on counts and widths that the 256 x 256 kernel takes (the shapes above
+# have moved to the mid-size kernel, which has no such tiles)
+@pytest.mark.parametrize("d,F,n", [(192, 12352, 257), (192, 12352, 288), (256, 8192, 513), (256, 8192, 544),
+                                   (320, 5120, 769), (320, 5120, 800), (256, 4160, 1025), (256, 4160, 1056)])
+def test_gateup_absorbed_rows_bitwise_wide(G, d, F, n):
+    K = TOK_KEEP
+    ref_n = n // 256 * 256 + 60
+    assert all(_absorbs(G, k, d, F) for k in (n, ref_n, ref_n + 64))
+    assert 1 <= n % 256 <= 32 < ref_n % 256
+    big = make_workload("tail", [[(ref_n, K)]], d=d, F=F, r_c=32, r_e=32, keep=0.5, dtype="bf16", seed=31)
+    small = _sub(big, [[(n, K)]], np.arange(n))
+    a_ref = _gateup(G, big)
+    a = _gateup(G, small)
+    print(f"[gateup tail wide d={d} F={F}] n={n} (tail {n % 256}) vs {ref_n}", flush=True)
+    np.testing.assert_array_equal(a, a_ref[:n])
+    a_cap = _gateup(G, small, cap=ref_n + 64)
+    np.testing.assert_array_equal(a_cap, a)
+
+
+@pytest.mark.parametrize("n0,n1", [(257, 260), (513, 40), (530, 1), (300, 288), (260, 513)])
+def test_gateup_absorbed_rows_two_sets_wide(G, n0, n1):
+    K, GK = TOK_KEEP, TOK_KEEP | TOK_GEN
+    d, F, r0, r1 = 256, 8192, 600, 600
+    assert _absorbs(G, n0 + n1, d, F, 2) and _absorbs(G, r0 + r1, d, F, 2)
+    big = make_workload("tail2", [[(r0, K)], [(r1, GK)]], d=d, F=F, r_c=32, r_e=32, keep=0.5, dtype="bf16", seed=32,
+                        n_sets=2)
+    rows = np.concatenate([np.arange(n0), r0 + np.arange(n1)])
+    small = _sub(big, [[(n0, K)], [(n1, GK)]], rows)
+    a_ref = _gateup(G, big)
+    a = _gateup(G, small)
+    np.testing.assert_array_equal(a[:n0], a_ref[:n0])
+    np.testing.assert_array_equal(a[n0:], a_ref[r0:r0 + n1])
 
 
 @pytest.mark.parametrize("n0,n1", [(257, 260), (260, 40), (530, 1), (300, 288)])
