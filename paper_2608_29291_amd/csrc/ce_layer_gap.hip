@@ -179,11 +179,12 @@ __global__ __launch_bounds__(kGapThreads) void gap_kernel(const int32_t* __restr
 }
 
 // 1024 threads a sequence and four tokens each per step for long sequences, else
-// 256 and one. Whole call at d 256, us, 256 and 1024 threads: 1 x 500 tokens 5.7
-// and 6.3, 1 x 1500 6.8 and 7.0, 4 x 1500 8.8 and 8.7, 4 x 2000 10.0 and 9.9, 4 x
-// 4224 15.7 and 13.8, 1 x 65536 94 and 52; more sequences than CUs lose: 512 x 500
-// 103.3 and 105.5.
-constexpr int kWideGap = 1536;
+// 256 and one. Stability and the whole gap at d 1536 in turn, us, the means with
+// 256 and 1024 threads: 1 x 300 tokens 10.9 and 11.7, 4 x 1000 14.8 and 14.9, 4 x
+// 1500 19.3 and 19.2, one of 4096 among three of 300 21.6 and 19.9, 4 x 4224 35.0
+// and 32.9; more sequences than CUs lose (512 x 500 at d 256: 103.3 and 105.5).
+// (The longest counts; the host knows the mean.)
+constexpr int kWideGap = 1024;
 
 hipError_t launch_gap(const float* cos_tok, const int32_t* seq_offsets, int B, int T, const int32_t* token_pos,
                       float delta, float* rho_all, float* rho_ret, float* gap, uint8_t* skip, hipStream_t stream) {

@@ -172,11 +172,13 @@ hipError_t launch_stability(const int32_t* seq_offsets, const uint8_t* flags, in
                             float* rda, hipStream_t stream) {
   if (B <= 0) return hipSuccess;
   // 1024 threads each only for long sequences: the lgammas of a wider workgroup
-  // cost more than its shorter loops save. us, 256 and 1024 threads: 4 x 500
-  // tokens 6.5 and 8.4, 4 x 2000 8.0 and 9.1, 4 x 4224 9.8 and 9.6, 1 x 16384 15.7
-  // and 12.1, 1 x 65536 34 and 22; two to a CU, 512 x 500: 7.9 and 16 (one token a
-  // step and nine lgammas a thread: 9.3, 10.7, 13, 25, 73 and 12)
-  constexpr int kWide = 4096;
+  // cost more than its shorter loops save. Stability and the layer gap at d 1536
+  // in turn, us, with 256 and 1024 threads: 1 x 300 tokens 11.7 and 13.4, 4 x 1000
+  // 14.9 and 16.7, 4 x 2000 22.9 and 23.6, three of 1341, 3379 and 1224 21.3 and
+  // 20.9, 16 x 3000 59.5 and 58.7, 4 x 4224 32.9 and 31.8; two workgroups to a CU,
+  // 512 x 500 alone: 7.9 and 16 (256 threads with one token a step and nine
+  // lgammas each: 12)
+  constexpr int kWide = 1792;
   if (wide_signal(B, T, kWide))
     hipLaunchKernelGGL(stability_kernel<1024>, dim3(B), dim3(1024), 0, stream, seq_offsets, flags, T, tp_t, tp_ref,
                        jaccard, j_rand, rda);

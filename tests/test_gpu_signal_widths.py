@@ -1,5 +1,5 @@
 """The per-sequence signal kernels at both workgroup widths (1024 threads for up
-to 256 sequences of 1536 tokens on average, the layer gap, or 4096, stability;
+to 256 sequences of 1024 tokens on average, the layer gap, or 1792, stability;
 256 threads else) over lengths around their steps of four tokens a thread. Bars: J bit-exact, J_rand and RDA 1e-6, the gap's means 2e-7."""
 import numpy as np
 import pytest
@@ -8,12 +8,12 @@ pytestmark = pytest.mark.gpu
 
 
 LENGTHS = {"short": [0, 1, 2, 7, 255, 256, 257, 1100],
-           "mid": [1023, 1024, 1025, 2047, 2049, 4095, 4097],  # 1536 to 4096 on average
-           "long": [4095, 4097, 8191, 8192, 8193, 12289]}
+           "mid": [255, 511, 1023, 1024, 1025, 2047, 2049],  # 1024 to 1792 on average
+           "long": [1023, 2049, 4095, 4097, 8191, 8192, 8193, 12289]}
 
 
-@pytest.mark.parametrize("nb,kind", [(3, "short"), (512, "short"), (513, "short"), (3, "mid"), (5, "long"),
-                                     (256, "mid"), (257, "mid")])
+@pytest.mark.parametrize("nb,kind", [(3, "short"), (512, "short"), (513, "short"), (40, "mid"), (5, "long"),
+                                     (256, "mid"), (257, "mid"), (31, "long")])
 def test_widths(nb, kind):
     import torch
     import paper_2608_29291_amd as ce
@@ -25,7 +25,7 @@ def test_widths(nb, kind):
     lens[0], lens[1] = 4097, 5000
     segs = [[(n, 1), (2, 2)] for n in lens]
     mean = sum(lens) / nb + 2
-    assert {"short": nb == 3 or mean < 1536, "mid": 1536 <= mean < 4096, "long": mean >= 4096}[kind]
+    assert {"short": nb == 3 or mean < 1024, "mid": 1024 <= mean < 1792, "long": mean >= 1792}[kind]
     run_case(segs, 0.4, 0.6, 0.3, nb)
     offs, flags = build_layout(segs)
     T, d = len(flags), 64
