@@ -674,7 +674,9 @@ def ce_layer_gap(batch: Batch, x_in, x_out, token_pos, delta, cos, rho_all, rho_
 
 def ce_routed_attention(q, k, v, o, q_offsets, kv_offsets, causal, scale, stream=None):
     """q, o [rows, H, head_dim], k, v [rows, H_kv, head_dim] bf16 device tensors;
-    q_offsets / kv_offsets int32 device tensors [B+1]."""
+    q_offsets / kv_offsets int32 device tensors [B+1]. A decode step's scratch
+    comes from torch's allocator, so a program that captures without
+    torch.cuda.graph keeps a workspace of its own (lib.ce_routed_attention_ws)."""
     for name, x in (("q", q), ("k", k)):
         if x is None or x.dim() != 3:
             raise ValueError(f"{name} must be [rows, heads, head_dim]")
@@ -694,7 +696,9 @@ def ce_routed_attention(q, k, v, o, q_offsets, kv_offsets, causal, scale, stream
         if stream is None:
             ws = torch.empty(need, dtype=_U8, device=q.device)
         else:
-            with torch.cuda.stream(stream):
+            # (any object with a raw handle is a stream here, as in every call)
+            with torch.cuda.stream(stream if isinstance(stream, torch.cuda.Stream)
+                                   else torch.cuda.ExternalStream(stream.cuda_stream)):
                 ws = torch.empty(need, dtype=_U8, device=q.device)
     _check(lib.ce_routed_attention_ws(ctypes.byref(at), ptrs[0], ptrs[1], ptrs[2], ptrs[3], _ptr(ws), need,
                                       _stream(stream)), "ce_routed_attention")

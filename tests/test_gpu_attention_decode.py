@@ -138,6 +138,13 @@ def test_own_stream_and_capture():
     ce.ce_routed_attention(*args, o, dqo, dko, True, DH ** -0.5, stream=side)
     side.synchronize()
     np.testing.assert_array_equal(G.host(o), want)
+    # a stream that is only its raw handle, as another library's wrapper has it
+    import types
+    o.zero_()
+    side.wait_stream(torch.cuda.current_stream())
+    ce.ce_routed_attention(*args, o, dqo, dko, True, DH ** -0.5, stream=types.SimpleNamespace(cuda_stream=side.cuda_stream))
+    side.synchronize()
+    np.testing.assert_array_equal(G.host(o), want)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         ce.ce_routed_attention(*args, o, dqo, dko, True, DH ** -0.5)
