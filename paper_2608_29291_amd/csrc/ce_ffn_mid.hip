@@ -17,7 +17,7 @@
 // from L2 into LDS. Measured, us, this kernel (down with its second launch) and
 // the 256 x 256 tiles: d 1536, d_ff 8960, gate/up 96 rows 16.8 and 32.5, 256
 // rows 24 and 37.5, 402 rows 34 and 38; down 96 rows 16 and 48, 402 rows 28 and
-// 64, 1024 rows 46 and 77, 2400 rows 92 and 99; d 3584, d_ff 18944, gate/up 96
+// 64, 1024 rows 46 and 77, 2400 rows 78 and 90; d 3584, d_ff 18944, gate/up 96
 // rows 71 and 94, 402 rows 139 and 155; down 96 rows 43 and 80, 256 rows 58 and
 // 101, 640 rows 120 and 135, 1600 rows 275 and 242 (not taken).
 #include <type_traits>
